@@ -17,9 +17,9 @@
 // Numbers.  Everything is FP64.  The seed at l0 = max(|mb|,|msky|) is formed
 // as a logarithm in double-double (Sec. 3.2 eq. logstart) and split into a
 // significand and a power of two.  While a chain's value is below 2^-900 it is
-// carried as d * 2^E with E < 0 and renormalised by exact powers of two every
-// RS_STEPS steps; once it reaches 2^-900 it is folded into a plain double (E = 0),
-// as Sec. 3.2 prescribes.  The checks are wave-uniform branches, so the inner
+// carried as d * 2^E with E < 0 a multiple of 900; every RS_STEPS steps a scaled chain
+// that has grown past 1 is multiplied by exactly 2^-900 (E += 900), and at E = 0 it is a
+// plain double, as Sec. 3.2 prescribes (its S = 2^90 with a larger step).  The checks are wave-uniform branches, so the inner
 // loop has no per-step branches.
 
 #include <hip/hip_runtime.h>
@@ -32,24 +32,20 @@ namespace {
 // Tile parameters (template arguments): R chains per lane, NT lanes per workgroup,
 // TB values of l per coefficient block; TR is kept in the tile triple (value 4) and no
 // longer shapes any kernel: the adjoint's row sums move every step.
-constexpr int TS = 8;         // steps between skip checks
+constexpr int TS = 8;         // steps per unrolled group
 constexpr int FOLD_EXP = -900;  // fold scaled values into plain doubles at 2^-900
 // A step of the normalised walk (below) multiplies max(|e^l|, |e^{l-1}|) by at most
 // alpha F0 |x - F1| + 1 <= 2 (l+1) 2 + 1 < 2^17 for l <= 16384 (F0 <= l+1, |x - F1| <= 2,
-// alpha <= 2), which bounds growth inside a TS block.
+// alpha <= 2).
 constexpr int GROWTH_BITS_PER_STEP = 17;
-// Scaled chains are rescaled (and folded) only every RS_STEPS steps: a rescaled chain
-// keeps max(|e|, |e_prev|) < 1, so its significand stays below 2^(17 RS_STEPS) = 2^544
-// until the next rescale, and a chain still scaled after one (true exponent below -900)
-// stays below 2^-356 until the next, where the skip test of a chain at 2^-100
-// (GROWTH_BITS_PER_STEP * TS bits of headroom) cannot fire.  Between rescales the skip
-// test looks at the plain chains only.
+// Chains are looked at every RS_STEPS steps.  A chain left scaled (E < 0) then is below 1 in its
+// own units, so its significand stays below 2^(17 RS_STEPS) = 2^544, and below 2^-900 in truth, so
+// it stays below 2^-356: it is not rescaled and not tested for the skip until the next look.
+// Plain chains are tested with the staged bound of the next RS_STEPS steps' growth (grow_bits).
 constexpr int RS_STEPS = 32;
-template <int TB>
-constexpr int rs_block() { static_assert(TB % TS == 0 && (TB % RS_STEPS == 0 || RS_STEPS % TB == 0), "tile"); return TB < RS_STEPS ? TB : RS_STEPS; }
-constexpr int SKIP_EXP_MAX = -(FOLD_EXP + GROWTH_BITS_PER_STEP * RS_STEPS) - GROWTH_BITS_PER_STEP * TS;  // 220
+constexpr int SKIP_EXP_MAX = -(FOLD_EXP + GROWTH_BITS_PER_STEP * RS_STEPS);  // 356
 static_assert(RS_STEPS % TS == 0 && GROWTH_BITS_PER_STEP * RS_STEPS < 1023 && SKIP_EXP_MAX >= 100,
-              "rescale period: no overflow of a scaled significand, no missed hot chain at skip 2^-100");
+              "look period: no overflow of a scaled significand, no missed hot chain at skip 2^-100");
 
 __device__ __forceinline__ bool wave_any(bool p) { return __ballot(p) != 0ull; }
 
@@ -94,11 +90,10 @@ constexpr int fwd_min_waves() { return NC == 1 ? min_waves<R>() : (R >= 4 ? 2 : 
 template <int R>
 constexpr int rows_min_waves() { return R >= 8 ? 2 : 4; }
 
-// The adjoint's LDS (about 37 KB per workgroup with TB = 32, 74 KB with TB = 64; mostly
-// the emitted row sums of two blocks) caps residency at 4 or 2 workgroups (waves per
-// SIMD) per CU.
+// The adjoint's LDS (46 KB per workgroup with TB = 32, 80 KB with TB = 64; mostly the emitted
+// row sums of two blocks) caps residency at 3 or 2 workgroups (waves per SIMD) per CU.
 template <int R, int TB>
-constexpr int adj_min_waves() { return min_waves<R>() < (TB >= 64 ? 2 : 4) ? min_waves<R>() : (TB >= 64 ? 2 : 4); }
+constexpr int adj_min_waves() { return min_waves<R>() < (TB >= 64 ? 2 : 3) ? min_waves<R>() : (TB >= 64 ? 2 : 3); }
 
 // ------------------------------------------------------------- double-double
 __device__ __forceinline__ void two_sum(double a, double b, double& s, double& e)
@@ -157,9 +152,9 @@ __device__ __forceinline__ SeedShape seed_shape(int mb, int ms)
 }
 
 // ln|d| = lnA + p ln c + q ln s in double-double, then d = 2^f * 2^k.
-// Returns the value in (d, E) form: E = 0 and d plain when |d| >= 2^-900,
-// otherwise d in [1, 2) and E = k < 0.  A zero base with a positive power gives
-// the zero chain (Sec. 3.2, the -infinity case).
+// Returns the value in (d, E) form, d * 2^E: E = 0 and d plain when |d| >= 2^-900, otherwise E a
+// negative multiple of 900 and |d| in [2^-899, 2).  A zero base with a positive power gives the
+// zero chain (Sec. 3.2, the -infinity case).
 __device__ __forceinline__ void seed_value(double lnAh, double lnAl, SeedShape sh,
                                            double lch, double lcl, double lsh, double lsl,
                                            double& d, int& E)
@@ -178,13 +173,8 @@ __device__ __forceinline__ void seed_value(double lnAh, double lnAl, SeedShape s
     const double f = (yh - k) + yl;
     const double m = exp2(f);
     const int ik = (int)k;
-    if (ik >= FOLD_EXP) {
-        d = ldexp(m, ik);
-        E = 0;
-    } else {
-        d = m;
-        E = ik;
-    }
+    E = ik >= FOLD_EXP ? 0 : ik / -FOLD_EXP * -FOLD_EXP;   // a multiple of 900, ik - E in (-900, 0]
+    d = ldexp(m, ik - E);
     if (sh.neg) d = -d;
 }
 
@@ -270,6 +260,89 @@ __device__ __forceinline__ NormCoef norm_coefs(int lb, int l0, int mb, int ms, i
     return NormCoef{alpha * A, alpha * nB, 1.0 / c};
 }
 
+// The same coefficients staged by the whole workgroup: lane tid takes l = lb + tid, so a block
+// is NT values of l and every wave stages 64 of them.  (With one wave staging a block of 64 while
+// the others wait at the barrier, the staging wave's SIMD is late in every block; the lanes also
+// share the square roots: each S(l) = sqrt(l^2 - mb^2) sqrt(l^2 - msky^2) is formed once, where
+// recursion_coefs takes four roots for each of two l.)  The products over segments and across them
+// take norm_coefs's order, so the coefficients are the same bit for bit.
+template <int NT>
+struct NormShared {
+    double edge[NT / 64 + 1][2];   // S at the last two l + 1 of each wave; [0]: of the block before
+    double tot[NT / NORM_SEG][2];  // product of m over a segment, per parity
+    double carry[2];               // c of the last two l of the block before
+};
+
+// Bits by which one step with coefficients A', nB' may grow max(|e^l|, |e^{l-1}|) (|x| <= 1).
+__device__ __forceinline__ int grow_bits(double A, double nB)
+{
+    return (__double2hiint(fabs(A) + fabs(nB) + 1.0) >> 20) - 1022;
+}
+
+struct NormLane {                  // what a lane keeps from one block to the next
+    double s, c;                   // S(l + 1), c_l
+};
+
+// grow[k] receives the largest grow_bits of the block's k-th RS_STEPS steps.
+// Two barriers inside; the caller's barrier after it has stored the coefficients ends the stage.
+// The first one also ends every wave's use of the block before.
+template <int NT>
+__device__ __forceinline__ NormCoef norm_coefs_group(int lb, int l0, int mb, int ms, int lmax, bool first,
+                                                     NormLane& st, NormShared<NT>& sh, int* grow)
+{
+    static_assert(NT % 64 == 0 && 64 % NORM_SEG == 0, "whole waves, whole segments");
+    const int tid = threadIdx.x, i = tid & 63, wave = tid >> 6;
+    const int l = lb + tid;
+    if (tid >= NT - 2) {           // first block: S(l0) = 0, c = 1 (S(l0 - 1) is not used)
+        sh.edge[0][tid - (NT - 2)] = first ? 0.0 : st.s;
+        sh.carry[tid - (NT - 2)] = first ? 1.0 : st.c;
+    }
+    const double ll = (double)l, l1 = (double)(l + 1);
+    const double b2 = (double)mb * (double)mb, s2 = (double)ms * (double)ms;
+    const double den = sqrt(l1 * l1 - b2) * sqrt(l1 * l1 - s2);
+    if (i >= 62) sh.edge[wave + 1][i - 62] = den;
+    __syncthreads();
+    double s0 = __shfl_up(den, 1, 64), sm = __shfl_up(den, 2, 64);   // S(l), S(l - 1)
+    if (i == 0) s0 = sh.edge[wave][1];
+    if (i < 2) sm = sh.edge[wave][i];
+    double A = 0.0, nB = 0.0, F2 = 0.0;
+    if (l < lmax) {
+        A = l1 * (2.0 * ll + 1.0) / den;
+        if (l > 0) {
+            nB = -(A * (((double)mb * (double)ms) / (ll * l1)));
+            F2 = (l1 * s0) / (ll * den);
+        }
+    }
+    double c = 1.0;                // c_l / c_{l-2}
+    if (l >= l0 + 2 && l <= lmax) c = 1.0 / ((ll * sm) / ((ll - 1.0) * s0));
+    const int j = i & (NORM_SEG - 1);
+#pragma unroll
+    for (int off = 2; off < NORM_SEG; off *= 2) {
+        const double v = __shfl_up(c, off, 64);
+        if (j >= off) c *= v;
+    }
+    const int seg = tid / NORM_SEG;
+    if (j >= NORM_SEG - 2) sh.tot[seg][tid & 1] = c;
+    __syncthreads();
+    double cr = sh.carry[tid & 1];
+#pragma unroll
+    for (int g = 0; g + 1 < NT / NORM_SEG; ++g)
+        if (g < seg) cr *= sh.tot[g][tid & 1];
+    c *= cr;
+    const double c_up = __shfl_up(c, 1, 64);
+    double c_next = __shfl_down(c, 1, 64);                        // c_{l+1}
+    if (i == 63) c_next = (l < lmax) ? (1.0 / F2) * c_up : c_up;  // as the next wave's first lane
+    const double alpha = c_next / c;
+    st.s = den;
+    st.c = c;
+    static_assert(NORM_SEG == RS_STEPS, "one growth bound per segment");
+    int g = grow_bits(alpha * A, alpha * nB);
+#pragma unroll
+    for (int off = NORM_SEG / 2; off > 0; off /= 2) g = max(g, __shfl_xor(g, off, 64));
+    if (j == 0) grow[seg] = g;
+    return NormCoef{alpha * A, alpha * nB, 1.0 / c};
+}
+
 // Binary exponent e of max(|d|, |d_prev|) (|v| in [2^(e-1), 2^e)); a zero value does
 // not count (the caller treats d = d_prev = 0 as the zero chain).
 __device__ __forceinline__ int chain_exponent(double d, double dp)
@@ -281,58 +354,58 @@ __device__ __forceinline__ int chain_exponent(double d, double dp)
     return max(d != 0.0 ? e1 : NONE, dp != 0.0 ? e2 : NONE);
 }
 
-// For plain chains (E = 0) the skip test of check_chain reduces to a threshold:
-// max(|d|, |d_prev|) >= 2^(-skip_exp - GROWTH_BITS_PER_STEP * TS).
+// The skip test of a wave's plain chains (E = 0): whether any may reach 2^-skip_exp within the next
+// RS_STEPS steps, each of which grows max(|d|, |d_prev|) by at most 2^bits.  Only high words are
+// compared (the threshold is a power of two): three integer operations a chain, where the maxima
+// of doubles take four and more with the operands' canonicalisation.  Testing every 8 steps with
+// 17 bits a step cost as many instructions as the skipped steps themselves (forward, lmax 4096:
+// 4.17 VALU operations per chain step, 3.6 of them multiply-adds).
 template <int R>
-__device__ __forceinline__ bool lane_may_be_hot(const double (&d)[R], const double (&dp)[R], double thr)
+__device__ __forceinline__ bool wave_may_be_hot(const double (&d)[R], const double (&dp)[R], const int (&E)[R],
+                                                bool scaled, int skip_exp, int bits)
 {
-    double m = 0.0;
+    unsigned m = 0;
 #pragma unroll
-    for (int r = 0; r < R; ++r) m = fmax(m, fmax(fabs(d[r]), fabs(dp[r])));
-    return m >= thr;
+    for (int r = 0; r < R; ++r) {
+        unsigned h = max((unsigned)__double2hiint(d[r]) & 0x7fffffffu, (unsigned)__double2hiint(dp[r]) & 0x7fffffffu);
+        if (scaled) h = E[r] == 0 ? h : 0u;
+        m = max(m, h);
+    }
+    return wave_any(m >= (unsigned)(1023 - skip_exp - bits * RS_STEPS) << 20);
 }
 
-// The same test between two rescales, while some chains are still scaled: those
-// cannot be hot yet (see RS_STEPS), and their d is in scaled units, so they are left out.
-template <int R>
-__device__ __forceinline__ bool lane_may_be_hot_plain(const double (&d)[R], const double (&dp)[R],
-                                                      const int (&E)[R], double thr)
-{
-    double m = 0.0;
-#pragma unroll
-    for (int r = 0; r < R; ++r) m = fmax(m, E[r] == 0 ? fmax(fabs(d[r]), fabs(dp[r])) : 0.0);
-    return m >= thr;
-}
-
-__device__ __forceinline__ double hot_threshold(int skip_exp)
-{
-    return ldexp(1.0, -skip_exp - GROWTH_BITS_PER_STEP * TS);
-}
-
-// One scale check of a chain (every RS_STEPS steps in the convolution walks, every
-// TS steps where each d is written out).  From the exponent e of max(|d|, |d_prev|)
-// it takes the true exponent te = E + e of the chain.
+// One scale check of a chain where each d is written out (every TS steps).  From the exponent e of
+// max(|d|, |d_prev|) it takes the true exponent te = E + e of the chain.
 //  - rescale: a scaled chain (E < 0) is folded into plain doubles once te reaches
-//    -900 (k = E), otherwise brought back to a significand near 1 (k = -e); the
-//    power of two k applied to (d, d_prev) is returned for the caller's sums.
-//  - returns whether |d| may reach 2^-skip_exp within the next TS steps (the walks
-//    take that test from the plain chains' magnitudes instead, every TS steps).
+//    -900 (k = E), otherwise brought back to a significand near 1 (k = -e).
 // Branch-free per chain; the callers' conditions are wave-uniform.
-__device__ __forceinline__ bool check_chain(double& d, double& dp, int& E, int skip_exp, bool rescale, int& k)
+__device__ __forceinline__ void check_chain(double& d, double& dp, int& E)
 {
     const bool nz = (d != 0.0) | (dp != 0.0);
     const int e = chain_exponent(d, dp);
     const int te = E + e;
-    k = 0;
-    if (rescale) {
-        const bool sc = nz & (E < 0);
-        const bool fold = te >= FOLD_EXP;
-        k = sc ? (fold ? E : -e) : 0;
-        E = sc ? (fold ? 0 : te) : E;
-        d = ldexp(d, k);
-        dp = ldexp(dp, k);
-    }
-    return nz & (te + GROWTH_BITS_PER_STEP * TS > -skip_exp);
+    const bool sc = nz & (E < 0);
+    const bool fold = te >= FOLD_EXP;
+    const int k = sc ? (fold ? E : -e) : 0;
+    E = sc ? (fold ? 0 : te) : E;
+    d = ldexp(d, k);
+    dp = ldexp(dp, k);
+}
+
+// Rescale of a scaled chain (every RS_STEPS steps of the convolution walks): once max(|d|, |d_prev|)
+// has reached 1 both are multiplied by exactly 2^-900 and E rises by 900, to a plain double at 0.
+// A chain still scaled afterwards is below 1, so below 2^-900 in truth, which is what RS_STEPS is
+// derived from.  Returns the factor (1 or 2^-900) for sums held in the chain's units.  About ten VALU
+// operations a chain where taking both exponents with frexp and renormalising took about 25.
+__device__ __forceinline__ double rescale_chain(double& d, double& dp, int& E)
+{
+    const unsigned h = max((unsigned)__double2hiint(d) & 0x7fffffffu, (unsigned)__double2hiint(dp) & 0x7fffffffu);
+    const bool up = (E < 0) & (h >= 0x3ff00000u);
+    const double f = up ? 0x1p-900 : 1.0;
+    E = up ? E - FOLD_EXP : E;
+    d *= f;
+    dp *= f;
+    return f;
 }
 
 // One wave stages a whole block, so that its square roots and divisions keep all lanes busy,
@@ -398,8 +471,7 @@ __global__ void __launch_bounds__(NT) k_wigner(const WignerArgs a)
                 bool any = false;
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    int k;
-                    check_chain(d[r], dp[r], E[r], 0, true, k);
+                    check_chain(d[r], dp[r], E[r]);
                     any |= (E[r] < 0);
                 }
                 scaled = wave_any(any);
@@ -479,20 +551,21 @@ __device__ __forceinline__ double4 output_weights(const RawW (&raw)[NP], int c, 
     return w;
 }
 
-// LDS slots of one l: {A, nB, F2, -}, then the general form's {w1r, w1i, w2r, w2i} per output
-// or the even / odd form's {w1r, w1i} of two outputs per slot.
+// LDS slots (16 bytes) of one l: {A, nB}, then per output {w1r, w1i} and, in the general form,
+// {w2r, w2i}.
 template <int NC, bool ROWS>
-constexpr int coef_slots() { return ROWS ? 1 + (NC + 1) / 2 : 1 + NC; }
+constexpr int coef_slots() { return ROWS ? 1 + NC : 1 + 2 * NC; }
 
 // The weights take the factor 1/c_l of the normalised walk.
 template <int NC, int NP>
-__device__ __forceinline__ void stage_block(const NormCoef& k, const RawW (&raw)[NP], int l, int ms, double4* slot)
+__device__ __forceinline__ void stage_block(const NormCoef& k, const RawW (&raw)[NP], int l, int ms, double2* slot)
 {
-    slot[0] = make_double4(k.A, k.nB, 0.0, 0.0);
+    slot[0] = make_double2(k.A, k.nB);
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
         const double4 w = output_weights<NC, NP>(raw, c, l, ms);
-        slot[1 + c] = make_double4(w.x * k.ic, w.y * k.ic, w.z * k.ic, w.w * k.ic);
+        slot[1 + 2 * c] = make_double2(w.x * k.ic, w.y * k.ic);
+        slot[2 + 2 * c] = make_double2(w.z * k.ic, w.w * k.ic);
     }
 }
 
@@ -525,42 +598,41 @@ __device__ __forceinline__ RawRows<NC> load_rows_raw(const FwdArgs& a, int l, in
 }
 
 template <int NC>
-__device__ __forceinline__ void stage_block_rows(const NormCoef& k, const RawRows<NC>& w, double4* slot)
+__device__ __forceinline__ void stage_block_rows(const NormCoef& k, const RawRows<NC>& w, double2* slot)
 {
-    slot[0] = make_double4(k.A, k.nB, 0.0, 0.0);
-    double wr[NC + 1], wi[NC + 1];
+    slot[0] = make_double2(k.A, k.nB);
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {   // conj(b) * s, as in pair_weights, times 1/c_l
-        wr[c] = (w.br[c] * w.sr + w.bi[c] * w.si) * k.ic;
-        wi[c] = (w.br[c] * w.si - w.bi[c] * w.sr) * k.ic;
-    }
-    wr[NC] = 0.0; wi[NC] = 0.0;
-#pragma unroll
-    for (int c = 0; c < NC; c += 2) slot[1 + c / 2] = make_double4(wr[c], wi[c], wr[c + 1], wi[c + 1]);
+    for (int c = 0; c < NC; ++c)     // conj(b) * s, as in pair_weights, times 1/c_l
+        slot[1 + c] = make_double2((w.br[c] * w.sr + w.bi[c] * w.si) * k.ic,
+                                   (w.br[c] * w.si - w.bi[c] * w.sr) * k.ic);
 }
 
 template <int R, int NC, bool ACC, int NS>
-__device__ __forceinline__ void fwd_steps(const double4 (*cf)[NS], int s0,
+__device__ __forceinline__ void fwd_steps(const double2 (*cf)[NS], int s0,
                                           const double (&x)[R], double (&d)[R], double (&dp)[R],
                                           double (&c1r)[NC][R], double (&c1i)[NC][R],
                                           double (&c2r)[NC][R], double (&c2i)[NC][R])
 {
 #pragma unroll
     for (int t = 0; t < TS; ++t) {
-        const double4 k = cf[s0 + t][0];
-        double4 w[NC];
+        const double2 k = cf[s0 + t][0];
+        double2 w1[NC], w2[NC];
+        if constexpr (ACC) {
 #pragma unroll
-        for (int c = 0; c < NC; ++c)
-            if (ACC) w[c] = cf[s0 + t][1 + c];
+            for (int c = 0; c < NC; ++c) {
+                w1[c] = cf[s0 + t][1 + 2 * c];
+                w2[c] = cf[s0 + t][2 + 2 * c];
+            }
+        }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            if (ACC) {
+            if constexpr (ACC) {
 #pragma unroll
                 for (int c = 0; c < NC; ++c) {
-                    c1r[c][r] = fma(w[c].x, d[r], c1r[c][r]);
-                    c1i[c][r] = fma(w[c].y, d[r], c1i[c][r]);
-                    c2r[c][r] = fma(w[c].z, d[r], c2r[c][r]);
-                    c2i[c][r] = fma(w[c].w, d[r], c2i[c][r]);
+                    c1r[c][r] = fma(w1[c].x, d[r], c1r[c][r]);
+                    c1i[c][r] = fma(w1[c].y, d[r], c1i[c][r]);
+                    c2r[c][r] = fma(w2[c].x, d[r], c2r[c][r]);
+                    c2i[c][r] = fma(w2[c].y, d[r], c2i[c][r]);
                 }
             }
             const double u = fma(x[r], k.x, k.y);
@@ -577,8 +649,8 @@ __device__ __forceinline__ void fwd_steps(const double4 (*cf)[NS], int s0,
 // step adds w1 d into one of two sums (2 instead of 4 fused multiply-adds per chain and
 // output).  The step parity is that of t (blocks and groups have even lengths): P0 += at
 // even t, P1 at odd t, in the c1 and c2 registers of the general form.
-template <int R, int NC, bool ACC, int NS>
-__device__ __forceinline__ void fwd_steps_rows(const double4 (*cf)[NS], int s0,
+template <int R, int NC, int NS>
+__device__ __forceinline__ void fwd_steps_rows(const double2 (*cf)[NS], int s0,
                                                const double (&x)[R], double (&d)[R], double (&dp)[R],
                                                double (&p0r)[NC][R], double (&p0i)[NC][R],
                                                double (&p1r)[NC][R], double (&p1i)[NC][R])
@@ -586,48 +658,35 @@ __device__ __forceinline__ void fwd_steps_rows(const double4 (*cf)[NS], int s0,
     // With one output, each step's coefficients and weights are read during the step before (more
     // outputs leave no registers for it: their walks read them at the step).
     constexpr bool AHEAD = NC == 1;
-    constexpr int NV = ACC ? (NC + 1) / 2 : 0;
-    double4 kn;
-    double4 vn[NV > 0 ? NV : 1];
-    if constexpr (AHEAD) {
-        kn = cf[s0][0];
+    double2 kn = cf[s0][0], vn[NC];
 #pragma unroll
-        for (int c = 0; c < NV; ++c) vn[c] = cf[s0][1 + c];
-    }
+    for (int c = 0; c < NC; ++c) vn[c] = cf[s0][1 + c];
 #pragma unroll
     for (int t = 0; t < TS; ++t) {
-        if constexpr (!AHEAD) {
+        if (!AHEAD && t > 0) {
             kn = cf[s0 + t][0];
 #pragma unroll
-            for (int c = 0; c < NV; ++c) vn[c] = cf[s0 + t][1 + c];
+            for (int c = 0; c < NC; ++c) vn[c] = cf[s0 + t][1 + c];
         }
-        const double4 k = kn;
-        double wr[NC], wi[NC];
-        if (ACC) {
+        const double2 k = kn;
+        double2 w[NC];
 #pragma unroll
-            for (int c = 0; c < NC; c += 2) {
-                const double4 v = vn[c / 2];
-                wr[c] = v.x; wi[c] = v.y;
-                if (c + 1 < NC) { wr[c + 1] = v.z; wi[c + 1] = v.w; }
-            }
-        }
+        for (int c = 0; c < NC; ++c) w[c] = vn[c];
         if (AHEAD && t + 1 < TS) {
             kn = cf[s0 + t + 1][0];
 #pragma unroll
-            for (int c = 0; c < NV; ++c) vn[c] = cf[s0 + t + 1][1 + c];
+            for (int c = 0; c < NC; ++c) vn[c] = cf[s0 + t + 1][1 + c];
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            if (ACC) {
 #pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    if ((t & 1) == 0) {
-                        p0r[c][r] = fma(wr[c], d[r], p0r[c][r]);
-                        p0i[c][r] = fma(wi[c], d[r], p0i[c][r]);
-                    } else {
-                        p1r[c][r] = fma(wr[c], d[r], p1r[c][r]);
-                        p1i[c][r] = fma(wi[c], d[r], p1i[c][r]);
-                    }
+            for (int c = 0; c < NC; ++c) {
+                if ((t & 1) == 0) {
+                    p0r[c][r] = fma(w[c].x, d[r], p0r[c][r]);
+                    p0i[c][r] = fma(w[c].y, d[r], p0i[c][r]);
+                } else {
+                    p1r[c][r] = fma(w[c].x, d[r], p1r[c][r]);
+                    p1i[c][r] = fma(w[c].y, d[r], p1i[c][r]);
                 }
             }
             const double u = fma(x[r], k.x, k.y);
@@ -638,21 +697,25 @@ __device__ __forceinline__ void fwd_steps_rows(const double4 (*cf)[NS], int s0,
     }
 }
 
-template <int TB, int NS>
+// One block of NT values of l: the workgroup stages it together, walks it, and stages the next
+// one over it (the stage's first barrier waits for the last reader).
+template <int NT, int NS>
 struct FwdShared {
-    double4 cf[2][TB][NS];   // coefficient slots of the current and the next block
-    double carry[2];         // c of the last two l of the latest staged block
+    double2 cf[NT][NS];      // coefficient slots of the block
+    NormShared<NT> norm;
+    int grow[NT / RS_STEPS]; // growth bounds of the block's steps
 };
 
 // One (column, ring tile) work item of the forward over pairs P0 .. P0 + NP - 1 into outputs
 // P0 .. P0 + NC - 1.  ROWS: the even / odd form, output c with beam row sign rows_sign[c].
-template <int R, int NT, int TB, int NC, int NP, bool ROWS, int P0, int NS>
+template <int R, int NT, int NC, int NP, bool ROWS, int P0, int NS>
 __device__ __forceinline__ void fwd_column_walk(const FwdArgs& a, int ci, int tile, const int* rows_sign,
-                                                FwdShared<TB, NS>& sh_)
+                                                FwdShared<NT, NS>& sh_)
 {
     static_assert(NC == 1 || NC == NP, "one output per pair, or one summed output");
     static_assert(!ROWS || NC == NP, "the even / odd form: one output per pair");
     static_assert(NS >= coef_slots<NC, ROWS>() && P0 + NP <= kMaxPairs, "coefficient slots, pairs");
+    static_assert(NT % RS_STEPS == 0 && RS_STEPS % TS == 0, "whole rescale periods per block");
     const int tid = threadIdx.x;
     const int mb = ldg(a.col.mb + ci), ms = ldg(a.col.ms + ci);
     const int L = a.lmax;
@@ -684,7 +747,6 @@ __device__ __forceinline__ void fwd_column_walk(const FwdArgs& a, int ci, int ti
     for (int r = 0; r < R; ++r) scaled |= (E[r] < 0);
     scaled = wave_any(scaled);
     bool acc_on = (a.skip_exp <= 0);
-    const double thr = hot_threshold(a.skip_exp);
 
     RawW raw[NP];         // general form: the loads of the next block, in flight during a block
     RawRows<NC> rraw;     // even / odd form
@@ -696,62 +758,50 @@ __device__ __forceinline__ void fwd_column_walk(const FwdArgs& a, int ci, int ti
             for (int p = 0; p < NP; ++p) raw[p] = load_weights_raw(a, P0 + p, l, mb, ms);
         }
     };
-    // the staging wave's lanes: l = lb + lane; the coefficients need all 64 lanes
-    const int lane = tid & 63;
-    auto stage_raw = [&](int lb, bool first, double4 (*slots)[NS]) {
-        const NormCoef k = norm_coefs<TB>(lb, l0, mb, ms, L, first, sh_.carry);
-        if (lane < TB) {
-            if constexpr (ROWS)
-                stage_block_rows<NC>(k, rraw, slots[lane]);
-            else
-                stage_block<NC, NP>(k, raw, lb + lane, ms, slots[lane]);
-        }
+    NormLane st;
+    auto stage_raw = [&](int lb, bool first) {
+        const NormCoef k = norm_coefs_group<NT>(lb, l0, mb, ms, L, first, st, sh_.norm, sh_.grow);
+        if constexpr (ROWS)
+            stage_block_rows<NC>(k, rraw, sh_.cf[tid]);
+        else
+            stage_block<NC, NP>(k, raw, lb + tid, ms, sh_.cf[tid]);
+        __syncthreads();
     };
-    if (stage_wave<NT>(tid, 0)) {
-        if (lane < TB) load_raw(l0 + lane);
-        stage_raw(l0, true, sh_.cf[0]);
-    }
-    __syncthreads();
-    constexpr int RS_BLK = rs_block<TB>();   // steps between rescales of scaled chains
-    const int nblk = (L - l0) / TB + 1;
-    for (int kb = 0; kb < nblk; ++kb) {
-        const int buf = kb & 1;
-        const int lb = l0 + kb * TB;
-        const bool stage = stage_wave<NT>(tid, kb + 1) && (kb + 1 < nblk);
-        if (stage && lane < TB) load_raw(lb + TB + lane);   // in flight during the block
-        for (int s1 = 0; s1 < TB; s1 += RS_BLK) {
+    load_raw(l0 + tid);
+    stage_raw(l0, true);
+    const int n = L - l0 + 1;              // l values of a chain
+    for (int b0 = 0; b0 < n; b0 += NT) {
+        const bool more = b0 + NT < n;
+        if (more) load_raw(l0 + b0 + NT + tid);     // in flight during the block
+        const int send = min(NT, n - b0);
+        for (int s1 = 0; s1 < send; s1 += RS_STEPS) {
             if (scaled) {
                 bool any = false;
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
-                    int k;
-                    (void)check_chain(d[r], dp[r], E[r], a.skip_exp, true, k);
+                    const double f = rescale_chain(d[r], dp[r], E[r]);
                     if (acc_on) {   // sums in the chain's scaled units follow it
 #pragma unroll
-                        for (int c = 0; c < NC; ++c) {
-                            c1r[c][r] = ldexp(c1r[c][r], k); c1i[c][r] = ldexp(c1i[c][r], k);
-                            c2r[c][r] = ldexp(c2r[c][r], k); c2i[c][r] = ldexp(c2i[c][r], k);
-                        }
+                        for (int c = 0; c < NC; ++c) { c1r[c][r] *= f; c1i[c][r] *= f; c2r[c][r] *= f; c2i[c][r] *= f; }
                     }
                     any |= (E[r] < 0);
                 }
                 scaled = wave_any(any);
             }
+            if (!acc_on) acc_on = wave_may_be_hot<R>(d, dp, E, scaled, a.skip_exp, sh_.grow[s1 / RS_STEPS]);
+            const int s2 = min(s1 + RS_STEPS, send);
             // kept rolled: unrolled, the 4-wave forward spills twice as many registers
 #pragma unroll 1
-            for (int s0 = s1; s0 < s1 + RS_BLK; s0 += TS) {
+            for (int s0 = s1; s0 < s2; s0 += TS) {
                 if (!acc_on)
-                    acc_on = wave_any(scaled ? lane_may_be_hot_plain<R>(d, dp, E, thr) : lane_may_be_hot<R>(d, dp, thr));
-                if (!acc_on)
-                    fwd_steps<R, NC, false>(sh_.cf[buf], s0, x, d, dp, c1r, c1i, c2r, c2i);
+                    fwd_steps<R, NC, false>(sh_.cf, s0, x, d, dp, c1r, c1i, c2r, c2i);
                 else if constexpr (ROWS)
-                    fwd_steps_rows<R, NC, true>(sh_.cf[buf], s0, x, d, dp, c1r, c1i, c2r, c2i);
+                    fwd_steps_rows<R, NC>(sh_.cf, s0, x, d, dp, c1r, c1i, c2r, c2i);
                 else
-                    fwd_steps<R, NC, true>(sh_.cf[buf], s0, x, d, dp, c1r, c1i, c2r, c2i);
+                    fwd_steps<R, NC, true>(sh_.cf, s0, x, d, dp, c1r, c1i, c2r, c2i);
             }
         }
-        if (stage) stage_raw(lb + TB, false, sh_.cf[buf ^ 1]);
-        __syncthreads();
+        if (more) stage_raw(l0 + b0 + NT, false);
     }
 
     if constexpr (ROWS) {
@@ -795,26 +845,26 @@ __device__ __forceinline__ int row_sign(const FwdArgs& a, int p, int mb)
 // The scalar forward runs as two launches over every (column, tile): k_fwd_rows takes the
 // columns whose beam rows are equal up to a sign, k_fwd the others (and every polarised
 // column); a workgroup whose column belongs to the other launch returns at once.
-template <int R, int NT, int TB, int NC, int NP>
+template <int R, int NT, int NC, int NP>
 __global__ void __launch_bounds__(NT, (fwd_min_waves<R, NC, NP>())) k_fwd(const FwdArgs a)
 {
-    __shared__ FwdShared<TB, 1 + NC> sh;
+    __shared__ FwdShared<NT, coef_slots<NC, false>()> sh;
     const int ci = blockIdx.x / a.ntile;
     if constexpr (NC == 1 && NP == 1) {
         if (a.beam_sym[0] && row_sign(a, 0, ldg(a.col.mb + ci)) != 0) return;
     }
     const int none[NC] = {};
-    fwd_column_walk<R, NT, TB, NC, NP, false, 0>(a, ci, blockIdx.x - ci * a.ntile, none, sh);
+    fwd_column_walk<R, NT, NC, NP, false, 0>(a, ci, blockIdx.x - ci * a.ntile, none, sh);
 }
 
-template <int R, int NT, int TB>
+template <int R, int NT>
 __global__ void __launch_bounds__(NT, (rows_min_waves<R>())) k_fwd_rows(const FwdArgs a)
 {
-    __shared__ FwdShared<TB, 2> sh;
+    __shared__ FwdShared<NT, coef_slots<1, true>()> sh;
     const int ci = blockIdx.x / a.ntile;
     const int s[1] = {row_sign(a, 0, ldg(a.col.mb + ci))};
     if (s[0] == 0) return;
-    fwd_column_walk<R, NT, TB, 1, 1, true, 0>(a, ci, blockIdx.x - ci * a.ntile, s, sh);
+    fwd_column_walk<R, NT, 1, 1, true, 0>(a, ci, blockIdx.x - ci * a.ntile, s, sh);
 }
 
 // Batched form: one workgroup per (walk, column, ring tile) item, the items in order of cost,
@@ -832,26 +882,26 @@ constexpr int walk_pairs() { return R >= 8 ? 2 : 4; }
 template <int R>
 constexpr int items_min_waves() { return R >= 4 ? 2 : 3; }
 
-template <int R, int NT, int TB, int NS, int P>
+template <int R, int NT, int NS, int P>
 __device__ __forceinline__ void fwd_item_alone(const FwdArgs& a, int ci, int tile, int k, const int (&s)[kMaxPairs],
-                                               FwdShared<TB, NS>& cf)
+                                               FwdShared<NT, NS>& cf)
 {
     if (P < k) {
         if (s[P] != 0)
-            fwd_column_walk<R, NT, TB, 1, 1, true, P>(a, ci, tile, s + P, cf);
+            fwd_column_walk<R, NT, 1, 1, true, P>(a, ci, tile, s + P, cf);
         else
-            fwd_column_walk<R, NT, TB, 1, 1, false, P>(a, ci, tile, s + P, cf);
+            fwd_column_walk<R, NT, 1, 1, false, P>(a, ci, tile, s + P, cf);
     }
 }
 
-template <int R, int NT, int TB>
+template <int R, int NT>
 __global__ void __launch_bounds__(NT, (items_min_waves<R>())) k_fwd_items(const FwdArgs* __restrict__ walks,
                                                                           const int* __restrict__ items)
 {
     constexpr int K = walk_pairs<R>();
     static_assert(K == 2 || K == 4, "walk sizes");
-    constexpr int NS = coef_slots<K, true>() > 2 ? coef_slots<K, true>() : 2;
-    __shared__ FwdShared<TB, NS> cf;
+    constexpr int NS = coef_slots<K, true>() > coef_slots<1, false>() ? coef_slots<K, true>() : coef_slots<1, false>();
+    __shared__ FwdShared<NT, NS> cf;
     const int* item = items + 3 * (size_t)blockIdx.x;
     const FwdArgs a = walks[item[0]];
     const int ci = item[1], tile = item[2];
@@ -868,19 +918,19 @@ __global__ void __launch_bounds__(NT, (items_min_waves<R>())) k_fwd_items(const 
         }
     }
     if (rows) {
-        if (k == 1) { fwd_column_walk<R, NT, TB, 1, 1, true, 0>(a, ci, tile, s, cf); return; }
-        if (k == 2) { fwd_column_walk<R, NT, TB, 2, 2, true, 0>(a, ci, tile, s, cf); return; }
+        if (k == 1) { fwd_column_walk<R, NT, 1, 1, true, 0>(a, ci, tile, s, cf); return; }
+        if (k == 2) { fwd_column_walk<R, NT, 2, 2, true, 0>(a, ci, tile, s, cf); return; }
         if constexpr (K == 4) {
-            if (k == 3) { fwd_column_walk<R, NT, TB, 3, 3, true, 0>(a, ci, tile, s, cf); return; }
-            fwd_column_walk<R, NT, TB, 4, 4, true, 0>(a, ci, tile, s, cf);
+            if (k == 3) { fwd_column_walk<R, NT, 3, 3, true, 0>(a, ci, tile, s, cf); return; }
+            fwd_column_walk<R, NT, 4, 4, true, 0>(a, ci, tile, s, cf);
             return;
         }
     }
-    fwd_item_alone<R, NT, TB, NS, 0>(a, ci, tile, k, s, cf);
-    fwd_item_alone<R, NT, TB, NS, 1>(a, ci, tile, k, s, cf);
+    fwd_item_alone<R, NT, NS, 0>(a, ci, tile, k, s, cf);
+    fwd_item_alone<R, NT, NS, 1>(a, ci, tile, k, s, cf);
     if constexpr (K == 4) {
-        fwd_item_alone<R, NT, TB, NS, 2>(a, ci, tile, k, s, cf);
-        fwd_item_alone<R, NT, TB, NS, 3>(a, ci, tile, k, s, cf);
+        fwd_item_alone<R, NT, NS, 2>(a, ci, tile, k, s, cf);
+        fwd_item_alone<R, NT, NS, 3>(a, ci, tile, k, s, cf);
     }
 }
 
@@ -919,15 +969,16 @@ __device__ __forceinline__ double row_shift_up(double v)
 template <int NT, int NC>
 constexpr int out_stride() { return (NT / 64) * 4 * 4 * NC + 2; }
 
-// The coefficient ring holds four blocks of TB l offsets plus a copy of its first TS
-// slots behind its end, so that the TS consecutive offsets of a step group never wrap.
+// The coefficient ring holds the last two staged blocks of NT l offsets plus a copy of its first
+// TS slots behind its end, so that the TS consecutive offsets of a step group never wrap.
 // NCMAX: the most cotangents a walk in this workgroup serves.
 template <int NT, int TB, int NCMAX>
 struct AdjShared {
-    double2 cfa[4 * TB + TS];                     // {A', nB'} per l offset, slot = offset mod 4 TB
-    double cic[4 * TB + TS];                      // 1 / c_l per l offset (the copy is not read)
+    double2 cfa[2 * NT + TS];                     // {A', nB'} per l offset, slot = offset mod 2 NT
+    double cic[2 * NT];                           // 1 / c_l per l offset
     double out[2 * TB * out_stride<NT, NCMAX>()]; // emitted row sums
-    double carry[2];                              // normalisation carry between blocks
+    NormShared<NT> norm;
+    int grow[2 * NT / RS_STEPS];                  // growth bounds, slot = offset / RS_STEPS mod 2 NT / RS_STEPS
 };
 
 template <int NT, int TB, int NCMAX>
@@ -938,11 +989,11 @@ constexpr size_t adj_lds_bytes() { return sizeof(AdjShared<NT, TB, NCMAX>); }
 template <int R, int NT, int TB, int NC, int NCMAX>
 __device__ __forceinline__ void adj_column(const AdjArgs& a, int ci, int tile, AdjShared<NT, TB, NCMAX>& sh_)
 {
-    static_assert(TB % TS == 0 && TS % 2 == 0 && TB >= ROW, "step groups: pairs of steps, TS per check");
+    static_assert(TB % RS_STEPS == 0 && NT % TB == 0 && TS % 2 == 0 && TB >= ROW, "step groups: pairs of steps, TS per check");
     static_assert(NC <= NCMAX && NC <= kMaxPairs, "cotangents per walk");
     constexpr int NW = NT / 64;
     constexpr int NS = 4 * NC;              // running sums per lane: (U re, U im, V re, V im) per cotangent
-    constexpr int CF_N = 4 * TB;            // coefficient ring: offset blocks kb-1, kb (read), kb+1 (staged)
+    constexpr int CF_N = 2 * NT;            // coefficient ring: the staged block of NT offsets and the one before
     constexpr int CF_MASK = CF_N - 1;
     constexpr int OUT_MASK = 2 * TB - 1;    // emitted sums: windows kb (written) and kb-1 (summed)
     constexpr int OS = out_stride<NT, NC>();
@@ -1001,22 +1052,19 @@ __device__ __forceinline__ void adj_column(const AdjArgs& a, int ci, int tile, A
     for (int r = 0; r < R; ++r) scaled |= (E[r] < 0);
     scaled = wave_any(scaled);
     bool acc_on = (a.skip_exp <= 0);    // wave-uniform
-    const double thr = hot_threshold(a.skip_exp);
 
     // one U and one V row per column and cotangent: ring tile 0 writes them, each later tile
     // (walked after it by the same workgroup) adds to them
     const size_t urow = packed_index(L, 0, ms);   // + l
 
-    auto stage = [&](int blk) {
-        if (stage_wave<NT>(tid, blk)) {
-            const NormCoef k = norm_coefs<TB>(l0 + blk * TB, l0, mb, ms, L, blk == 0, sh_.carry);
-            if (lane < TB) {
-                const int slot = (blk * TB + lane) & CF_MASK;
-                sh_.cfa[slot] = make_double2(k.A, k.nB);
-                sh_.cic[slot] = k.ic;
-                if (slot < TS) sh_.cfa[CF_N + slot] = make_double2(k.A, k.nB);   // the copy behind the ring's end
-            }
-        }
+    NormLane st;
+    auto stage = [&](int off, bool first) {   // offsets off .. off + NT - 1, off a multiple of NT
+        const int slot = (off + tid) & CF_MASK;
+        const NormCoef k = norm_coefs_group<NT>(l0 + off, l0, mb, ms, L, first, st, sh_.norm,
+                                                sh_.grow + (off & CF_MASK) / RS_STEPS);
+        sh_.cfa[slot] = make_double2(k.A, k.nB);
+        sh_.cic[slot] = k.ic;
+        if (slot < TS) sh_.cfa[CF_N + slot] = make_double2(k.A, k.nB);   // the copy behind the ring's end
     };
     // Lane 15 of each row stores the sums that leave it.  The sums alternate between two
     // register sets step by step, so that the two sums a pair of steps completes are both
@@ -1076,31 +1124,36 @@ __device__ __forceinline__ void adj_column(const AdjArgs& a, int ci, int tile, A
         }
     };
 
-    stage(0);
+    stage(0, true);
     __syncthreads();
-    constexpr int RS_BLK = rs_block<TB>();   // steps between rescales of scaled chains
-    // lane 15 of a row finishes l = L at time n - 1 + SKEW
-    const int nblk = (n + SKEW + TB - 1) / TB;
-    for (int kb = 0; kb < nblk; ++kb) {
-        const int buf_t = kb * TB;
-        for (int s1 = 0; s1 < TB; s1 += RS_BLK) {
+    // lane 15 of a row finishes l = L at time n - 1 + SKEW; the last block runs whole step groups
+    const int T = n + SKEW;
+    for (int buf_t = 0; buf_t < T; buf_t += TB) {
+        const int send = min(TB, T - buf_t);
+        for (int s1 = 0; s1 < send; s1 += RS_STEPS) {
             if (scaled) {
                 bool any = false;
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     const bool was = E[r] < 0;
-                    int k;
-                    (void)check_chain(d[r], dp[r], E[r], a.skip_exp, true, k);
+                    (void)rescale_chain(d[r], dp[r], E[r]);
                     if (was && E[r] == 0) load_g(r);
                     any |= (E[r] < 0);
                 }
                 scaled = wave_any(any);
             }
-            for (int s0 = s1; s0 < s1 + RS_BLK; s0 += TS) {
+            // a lane that has not started yet holds its seed, so the test covers it; lanes trail
+            // by up to 15 steps, so the bound of the offsets before counts as well
+            if (!acc_on) {
+                constexpr int GROW_N = CF_N / RS_STEPS;
+                const int gs = (buf_t + s1) / RS_STEPS;
+                int bits = sh_.grow[gs % GROW_N];
+                if (gs > 0) bits = max(bits, sh_.grow[(gs - 1) % GROW_N]);
+                acc_on = wave_may_be_hot<R>(d, dp, E, scaled, a.skip_exp, bits);
+            }
+            const int s2 = min(s1 + RS_STEPS, send);
+            for (int s0 = s1; s0 < s2; s0 += TS) {
                 const int t0 = buf_t + s0;   // row time of the group's first step
-                // a lane that has not started yet holds its seed, so the test covers it
-                if (!acc_on)
-                    acc_on = wave_any(scaled ? lane_may_be_hot_plain<R>(d, dp, E, thr) : lane_may_be_hot<R>(d, dp, thr));
                 if (t0 < SKEW) {
                     // start of the walk: lane k holds its chain (seed, 0) until time k and adds nothing
 #pragma unroll
@@ -1167,10 +1220,11 @@ __device__ __forceinline__ void adj_column(const AdjArgs& a, int ci, int tile, A
                 }
             }
         }
-        if (kb + 1 < nblk) stage(kb + 1);
+        const int next = buf_t + TB;
+        if ((next & (NT - 1)) == 0 && next < T) stage(next, false);
         __syncthreads();
-        // window kb: the sums of l offsets kb TB - 15 .. (kb+1) TB - 16, all emitted in this
-        // block; the waves and rows in a fixed order (the next block writes the other window)
+        // the sums of l offsets buf_t - 15 .. buf_t + TB - 16, all emitted in this block; the waves
+        // and rows in a fixed order (the next block writes the other window)
         for (int q = tid; q < TB * NS; q += NT) {
             const int o = buf_t - SKEW + q / NS, comp = q % NS;
             if (o >= 0 && o < n) {
@@ -1407,11 +1461,8 @@ int launch_wigner(const WignerArgs& a, Tile t, void* stream)
 }
 
 // Maps a runtime (R, TB[, TR]) onto the template instantiation F<R, TB[, TR]>.
-#define TC_FWD_VARIANTS(X) X(2, 32) X(4, 32) X(8, 32) X(2, 64) X(4, 64) X(8, 64)
-#define TC_FWDPOL_VARIANTS(X)                                                                   \
-    X(2, 32, 1, 2) X(4, 32, 1, 2) X(2, 64, 1, 2) X(4, 64, 1, 2) X(2, 32, 1, 3) X(4, 32, 1, 3)  \
-    X(2, 64, 1, 3) X(4, 64, 1, 3) X(2, 32, 2, 2) X(4, 32, 2, 2) X(2, 64, 2, 2) X(4, 64, 2, 2)  \
-    X(2, 32, 3, 3) X(4, 32, 3, 3) X(2, 64, 3, 3) X(4, 64, 3, 3)
+#define TC_FWD_VARIANTS(X) X(2) X(4) X(8)
+#define TC_FWDPOL_VARIANTS(X) X(2, 1, 2) X(4, 1, 2) X(2, 1, 3) X(4, 1, 3) X(2, 2, 2) X(4, 2, 2) X(2, 3, 3) X(4, 3, 3)
 #define TC_ADJ_VARIANTS(X) X(2, 32, 4) X(4, 32, 4) X(8, 32, 4) X(2, 64, 4) X(4, 64, 4) X(8, 64, 4)
 
 int launch_beam_symmetry(const double* blm, int lmax, int mbmax, int* sym, void* stream)
@@ -1425,22 +1476,22 @@ int launch_fwd(const FwdArgs& a, Tile t, void* stream)
 {
     const int blocks = a.ncol * a.ntile;
     if (a.npair == 1) {
-#define X(r, tb)                                                                              \
-    if (t.R == r && t.TB == tb) {                                                             \
+#define X(r)                                                                                  \
+    if (t.R == r) {                                                                           \
         if (a.beam_sym[0]) {                                                                  \
-            const int rc = launch_grid(k_fwd_rows<r, 256, tb>, a, blocks, 256, stream);       \
+            const int rc = launch_grid(k_fwd_rows<r, 256>, a, blocks, 256, stream);           \
             if (rc) return rc;                                                                \
         }                                                                                     \
-        return launch_grid(k_fwd<r, 256, tb, 1, 1>, a, blocks, 256, stream);                  \
+        return launch_grid(k_fwd<r, 256, 1, 1>, a, blocks, 256, stream);                      \
     }
         TC_FWD_VARIANTS(X)
 #undef X
         return (int)hipErrorInvalidValue;
     }
     const int nc = a.sum ? 1 : a.npair;
-#define X(r, tb, c, p)                                                        \
-    if (t.R == r && t.TB == tb && nc == c && a.npair == p)                    \
-        return launch_grid(k_fwd<r, 256, tb, c, p>, a, blocks, 256, stream);
+#define X(r, c, p)                                             \
+    if (t.R == r && nc == c && a.npair == p)                   \
+        return launch_grid(k_fwd<r, 256, c, p>, a, blocks, 256, stream);
     TC_FWDPOL_VARIANTS(X)
 #undef X
     return (int)hipErrorInvalidValue;
@@ -1481,10 +1532,10 @@ int launch_fwd_items(const FwdArgs* walks, const int* items, int nitems, Tile t,
 {
     if (nitems <= 0) return 0;
     hipStream_t s = (hipStream_t)stream;
-#define X(r, tb)                                                                                             \
-    if (t.R == r && t.TB == tb) {                                                                            \
-        hipLaunchKernelGGL((k_fwd_items<r, 256, tb>), dim3(nitems), dim3(256), 0, s, walks, items);            \
-        return (int)hipGetLastError();                                                                       \
+#define X(r)                                                                                             \
+    if (t.R == r) {                                                                                      \
+        hipLaunchKernelGGL((k_fwd_items<r, 256>), dim3(nitems), dim3(256), 0, s, walks, items);          \
+        return (int)hipGetLastError();                                                                   \
     }
     TC_FWD_VARIANTS(X)
 #undef X
