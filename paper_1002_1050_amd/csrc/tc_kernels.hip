@@ -262,14 +262,19 @@ __device__ __forceinline__ NormCoef norm_coefs(int lb, int l0, int mb, int ms, i
 
 // The same coefficients staged by the whole workgroup: lane tid takes l = lb + tid, so a block
 // is NT values of l and every wave stages 64 of them.  (With one wave staging a block of 64 while
-// the others wait at the barrier, the staging wave's SIMD is late in every block; the lanes also
-// share the square roots: each S(l) = sqrt(l^2 - mb^2) sqrt(l^2 - msky^2) is formed once, where
-// recursion_coefs takes four roots for each of two l.)  The products over segments and across them
-// take norm_coefs's order, so the coefficients are the same bit for bit.
+// the others wait at the barrier, the staging wave's SIMD is late in every block.)
+//
+// With S(l) = sqrt((l^2 - mb^2)(l^2 - msky^2)) the closed forms are F0_l = (l+1)(2l+1) / S(l+1) and
+// F2_l = (l+1) S(l) / (l S(l+1)), so c_l / c_{l-2} = (l-1) S(l) / (l S(l-1)).  A lane takes the root at
+// l + 1 and its reciprocal by a joint iteration and gets those at l from its neighbour; the
+// quotients come from these reciprocals with one correction, to within rounding of the correctly
+// rounded ones.  (Products with the reciprocals alone, uncorrected, were 0.5% faster at lmax 4096
+// and doubled the error of C and of the gradients.)  About a third of norm_coefs's operations,
+// with one root in place of eight.
 template <int NT>
 struct NormShared {
-    double edge[NT / 64 + 1][2];   // S at the last two l + 1 of each wave; [0]: of the block before
-    double tot[NT / NORM_SEG][2];  // product of m over a segment, per parity
+    double edge[NT / 64 + 1][3];   // S(l+1), 1/S(l+1), c_{l+1} / c_{l-1} of a wave's last l; [0]: of the block before
+    double tot[NT / NORM_SEG][2];  // product of c_l / c_{l-2} over a segment, per parity
     double carry[2];               // c of the last two l of the block before
 };
 
@@ -279,8 +284,57 @@ __device__ __forceinline__ int grow_bits(double A, double nB)
     return (__double2hiint(fabs(A) + fabs(nB) + 1.0) >> 20) - 1022;
 }
 
+// 1 / a for normal a: the hardware's estimate (relative error 2^-24) and two Newton steps.
+__device__ __forceinline__ double rcp_newton(double a)
+{
+    double y = __builtin_amdgcn_rcp(a);
+    y = fma(y, fma(-a, y, 1.0), y);
+    return fma(y, fma(-a, y, 1.0), y);
+}
+
+// sqrt(p) and 1 / sqrt(p) for normal p > 0: the hardware's estimate of the reciprocal root, two
+// joint Newton (Goldschmidt) steps, one correction of each.
+__device__ __forceinline__ void sqrt_and_rsqrt(double p, double& root, double& recip)
+{
+    const double y = __builtin_amdgcn_rsq(p);
+    double g = p * y, h = 0.5 * y;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const double r = fma(-h, g, 0.5);
+        g = fma(g, r, g);
+        h = fma(h, r, h);
+    }
+    g = fma(fma(-g, g, p), h, g);
+    h = fma(h, fma(-h, g, 0.5), h);
+    root = g;
+    recip = 2.0 * h;
+}
+
+// a / b given y = 1 / b to a few ulp.
+__device__ __forceinline__ double div_corrected(double a, double b, double y)
+{
+    const double q = a * y;
+    return fma(fma(-b, q, a), y, q);
+}
+
+// The value of v in lane addr / 4.
+__device__ __forceinline__ double lane_value(int addr, double v)
+{
+    return __hiloint2double(__builtin_amdgcn_ds_bpermute(addr, __double2hiint(v)),
+                            __builtin_amdgcn_ds_bpermute(addr, __double2loint(v)));
+}
+
+// The value N lanes below in the row of 16, 1 where there is none.
+template <int N>
+__device__ __forceinline__ double row_below_or_one(double v)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x110 + N, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0x3ff00000, __double2hiint(v), 0x110 + N, 0xF, 0xF, false);
+    return __hiloint2double(hi, lo);
+}
+
 struct NormLane {                  // what a lane keeps from one block to the next
-    double s, c;                   // S(l + 1), c_l
+    double S, rS, m, c;            // S(l + 1), its reciprocal, c_{l+1} / c_{l-1}, c_l
 };
 
 // grow[k] receives the largest grow_bits of the block's k-th RS_STEPS steps.
@@ -290,57 +344,61 @@ template <int NT>
 __device__ __forceinline__ NormCoef norm_coefs_group(int lb, int l0, int mb, int ms, int lmax, bool first,
                                                      NormLane& st, NormShared<NT>& sh, int* grow)
 {
-    static_assert(NT % 64 == 0 && 64 % NORM_SEG == 0, "whole waves, whole segments");
+    static_assert(NT % 64 == 0 && NORM_SEG == 32, "whole waves, segments of two rows");
+    static_assert(NORM_SEG == RS_STEPS, "one growth bound per segment");
     const int tid = threadIdx.x, i = tid & 63, wave = tid >> 6;
     const int l = lb + tid;
-    if (tid >= NT - 2) {           // first block: S(l0) = 0, c = 1 (S(l0 - 1) is not used)
-        sh.edge[0][tid - (NT - 2)] = first ? 0.0 : st.s;
-        sh.carry[tid - (NT - 2)] = first ? 1.0 : st.c;
+    if (tid >= NT - 2) sh.carry[tid - (NT - 2)] = first ? 1.0 : st.c;   // first block: c = 1
+    if (tid == NT - 1) {           // not used by a first block
+        sh.edge[0][0] = st.S; sh.edge[0][1] = st.rS; sh.edge[0][2] = st.m;
     }
-    const double ll = (double)l, l1 = (double)(l + 1);
-    const double b2 = (double)mb * (double)mb, s2 = (double)ms * (double)ms;
-    const double den = sqrt(l1 * l1 - b2) * sqrt(l1 * l1 - s2);
-    if (i >= 62) sh.edge[wave + 1][i - 62] = den;
+    const double ll = (double)l, l1 = ll + 1.0;
+    const double b2 = (double)mb * (double)mb, s2 = (double)ms * (double)ms, ll1 = l1 * l1;
+    const double rl1 = rcp_newton(l1);
+    double S, rS;
+    sqrt_and_rsqrt((ll1 - b2) * (ll1 - s2), S, rS);
+    const int below = ((i - 1) & 63) * 4;
+    const double S0 = lane_value(below, S), rS0 = lane_value(below, rS);   // at l
+    double rl = lane_value(below, rl1);
+    double m_next = div_corrected(ll * S, l1 * S0, rl1 * rS0);   // c_{l+1} / c_{l-1}
+    if (i == 63) { sh.edge[wave + 1][0] = S; sh.edge[wave + 1][1] = rS; sh.edge[wave + 1][2] = m_next; }
     __syncthreads();
-    double s0 = __shfl_up(den, 1, 64), sm = __shfl_up(den, 2, 64);   // S(l), S(l - 1)
-    if (i == 0) s0 = sh.edge[wave][1];
-    if (i < 2) sm = sh.edge[wave][i];
-    double A = 0.0, nB = 0.0, F2 = 0.0;
+    if (i == 0) {
+        rl = rcp_newton(ll);
+        m_next = div_corrected(ll * S, l1 * sh.edge[wave][0], rl1 * sh.edge[wave][1]);
+    }
+    double m = lane_value(below, m_next);                        // c_l / c_{l-2}
+    if (i == 0) m = sh.edge[wave][2];
+    double c = (l >= l0 + 2 && l <= lmax) ? m : 1.0;
+    double A = 0.0, nB = 0.0;
     if (l < lmax) {
-        A = l1 * (2.0 * ll + 1.0) / den;
-        if (l > 0) {
-            nB = -(A * (((double)mb * (double)ms) / (ll * l1)));
-            F2 = (l1 * s0) / (ll * den);
-        }
+        A = div_corrected(l1 * (2.0 * ll + 1.0), S, rS);
+        if (l > 0) nB = -(A * div_corrected((double)mb * (double)ms, ll * l1, rl * rl1));
     }
-    double c = 1.0;                // c_l / c_{l-2}
-    if (l >= l0 + 2 && l <= lmax) c = 1.0 / ((ll * sm) / ((ll - 1.0) * s0));
+    // products over the lanes of one parity within the segment: within rows of 16, then across
+    c *= row_below_or_one<2>(c);
+    c *= row_below_or_one<4>(c);
+    c *= row_below_or_one<8>(c);
     const int j = i & (NORM_SEG - 1);
-#pragma unroll
-    for (int off = 2; off < NORM_SEG; off *= 2) {
-        const double v = __shfl_up(c, off, 64);
-        if (j >= off) c *= v;
-    }
+    const double row_end = lane_value(((i & 32) + 14 + (i & 1)) * 4, c);   // the segment's first row
+    if (j >= 16) c *= row_end;
     const int seg = tid / NORM_SEG;
     if (j >= NORM_SEG - 2) sh.tot[seg][tid & 1] = c;
     __syncthreads();
     double cr = sh.carry[tid & 1];
-#pragma unroll
-    for (int g = 0; g + 1 < NT / NORM_SEG; ++g)
-        if (g < seg) cr *= sh.tot[g][tid & 1];
-    c *= cr;
-    const double c_up = __shfl_up(c, 1, 64);
-    double c_next = __shfl_down(c, 1, 64);                        // c_{l+1}
-    if (i == 63) c_next = (l < lmax) ? (1.0 / F2) * c_up : c_up;  // as the next wave's first lane
-    const double alpha = c_next / c;
-    st.s = den;
-    st.c = c;
-    static_assert(NORM_SEG == RS_STEPS, "one growth bound per segment");
+    for (int g = 0; g < 2 * wave; ++g) cr *= sh.tot[g][tid & 1];
+    const double t0 = sh.tot[2 * wave][tid & 1];
+    c *= (i < NORM_SEG) ? cr : cr * t0;
+    const double c_below = lane_value(below, c);
+    double c_next = lane_value(((i + 1) & 63) * 4, c);        // c_{l+1}
+    if (i == 63) c_next = (l < lmax) ? m_next * c_below : c_below;   // as the next wave's first lane
+    const double ic = rcp_newton(c), alpha = div_corrected(c_next, c, ic);
+    st.S = S; st.rS = rS; st.m = m_next; st.c = c;
     int g = grow_bits(alpha * A, alpha * nB);
 #pragma unroll
     for (int off = NORM_SEG / 2; off > 0; off /= 2) g = max(g, __shfl_xor(g, off, 64));
     if (j == 0) grow[seg] = g;
-    return NormCoef{alpha * A, alpha * nB, 1.0 / c};
+    return NormCoef{alpha * A, alpha * nB, ic};
 }
 
 // Binary exponent e of max(|d|, |d_prev|) (|v| in [2^(e-1), 2^e)); a zero value does
