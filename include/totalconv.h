@@ -311,7 +311,11 @@ int tc_set_tile_ex(int op, int R, int TB, int TR);
 /* The R that the next call of `op` at this lmax would use. */
 int tc_get_tile(int op, int lmax);
 
-/* The full tile (R, TB, TR) that the next call of `op` at this lmax would use. */
+/*
+ * The full tile (R, TB, TR) of op at this lmax: as set, else the built-in one for rings that fill
+ * its workgroups.  Where R is not set, a convolution call picks R (2, 4 or 8) and the lanes per
+ * workgroup (64, 128 or 256; TB is 32 below 256 in the adjoint) by its number of ring slots.
+ */
 int tc_get_tile_ex(int op, int lmax, int* R, int* TB, int* TR);
 
 /*

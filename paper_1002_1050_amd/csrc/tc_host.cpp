@@ -98,9 +98,7 @@ int g_matrix_R = 0;   // rows per lane of wigner_d_matrix (tc_set_tile); 0 = bui
 
 tc::Tile default_tile(int op, int lmax)
 {
-    // Built-in choice from a sweep at lmax 4096 / mbmax 14 on MI355X: the forward
-    // prefers 4 chains per lane (3 waves per SIMD for the general form, 4 for the even /
-    // odd form) with 64-l blocks, the adjoint 8.
+    // R of plans, TB of every call, and what tc_get_tile reports (plain calls take R by walk_cost).
     tc::Tile t{4, 256, 32, 4};
     if (op == TC_OP_FWD) t = lmax >= 256 ? tc::Tile{4, 256, 64, 4} : tc::Tile{2, 256, 32, 4};
     if (op == TC_OP_ADJ) t = lmax >= 256 ? tc::Tile{8, 256, 64, 4} : tc::Tile{2, 256, 32, 4};
@@ -112,6 +110,63 @@ tc::Tile default_tile(int op, int lmax)
         if (o.TR > 0) t.TR = o.TR;
     }
     return t;
+}
+
+int count_slots(int nring, const double* x)
+{
+    if (!x) return nring;   // size queries: at most nring slots
+    int n = 0;
+    for (int j = 0; j < nring; ++j) {
+        const int jp = nring - 1 - j;
+        if (j < jp && x[jp] == -x[j]) ++n;          // pair (j, jp)
+        else if (j > jp && x[j] == -x[jp]) continue;  // partner of an earlier pair
+        else ++n;                                   // single ring
+    }
+    return n;
+}
+
+// Cost of a walk over nslot ring slots with R chains per lane and NT lanes, in slots of a walk
+// without overheads.  The terms, each fitted to timings over 65 to 4096 slots on MI355X:
+//  - the slots of whole ring tiles (idle chains walk too);
+//  - a lane's cost per chain and step: the forward reads a step's coefficients from LDS once for R
+//    chains (R 2 is bound by it), the adjoint moves its sums once for R chains (6 + 8 / R operations);
+//  - the wave is the unit of the skip test: 64 R slots leave the skipped range together, so wide
+//    waves on few slots skip less;
+//  - staging and the block sums, per block of NT steps, over the NT R chains that share them.
+double walk_cost(int op, int R, int NT, int nslot)
+{
+    const bool adj = op == TC_OP_ADJ;
+    const double step = adj ? 6.0 + 8.0 / R : 5.0;
+    const double lane = adj ? step / 7.0 : (R >= 8 ? 1.0 : R >= 4 ? 1.01 : 1.15);
+    const double skip = 1.0 + (adj ? 0.12 : 0.25) * 64.0 * R / nslot;
+    const double stage = 1.0 + (adj ? 440.0 : 200.0) / (NT * R * step);
+    const int ntile = (nslot + NT * R - 1) / (NT * R);
+    return (double)ntile * NT * R * lane * skip * stage;
+}
+
+// The tile of a call over nslot ring slots: R as set or, at 0, the cheapest built one, with the
+// cheapest number of lanes per workgroup for it.
+tc::Tile fit_tile(int op, tc::Tile t, int nslot)
+{
+    const int R0 = t.R;
+    double best = 0.0;
+    for (int R : {8, 4, 2}) {
+        if ((R0 > 0 && R != R0) || (op == TC_OP_FWD_POL && R > 4)) continue;
+        for (int NT : {256, 128, 64}) {
+            const double c = walk_cost(op, R, NT, nslot);
+            if (best == 0.0 || c < best) { best = c; t.R = R; t.NT = NT; }
+        }
+    }
+    if (op == TC_OP_ADJ && t.NT < 256) t.TB = 32;   // the blocks the smaller workgroups are built with
+    return t;
+}
+
+// The tile of a plain convolution call: the built-in choice goes by the call's ring slots.
+tc::Tile call_tile(int op, int lmax, int nslot)
+{
+    tc::Tile t = default_tile(op, lmax);
+    t.R = g_tile_override[op].R;
+    return fit_tile(op, t, nslot);
 }
 
 // ------------------------------------------------------------ kernel timing
@@ -158,19 +213,6 @@ struct Layout {
     int nslot = 0, ncol = 0, ntile = 0;
     long long P = 0;
 };
-
-int count_slots(int nring, const double* x)
-{
-    if (!x) return nring;   // size queries: at most nring slots
-    int n = 0;
-    for (int j = 0; j < nring; ++j) {
-        const int jp = nring - 1 - j;
-        if (j < jp && x[jp] == -x[j]) ++n;          // pair (j, jp)
-        else if (j > jp && x[j] == -x[jp]) continue;  // partner of an earlier pair
-        else ++n;                                   // single ring
-    }
-    return n;
-}
 
 Layout make_layout(int op, int lmax, int mbmax_or_npair, int nring, const double* x, tc::Tile t)
 {
@@ -431,7 +473,7 @@ int fwd_impl(int op, int lmax, int mbmax, int nring, const double* cosbeta, int 
         if (!C[c]) return fail(TC_EINVAL, "C of output %d is NULL", c);
         if (!aligned16(C[c])) return fail(TC_EINVAL, "complex arrays must be 16-byte aligned");
     }
-    const tc::Tile t = default_tile(op, lmax);
+    const tc::Tile t = call_tile(op, lmax, count_slots(nring, cosbeta));
     const Layout L = make_layout(op, lmax, mbmax, nring, cosbeta, t);
     if ((rc = check_ws(L, workspace, ws_bytes)) || (rc = check_grid(L))) return rc;
     auto build = [&](std::vector<char>& img) {
@@ -490,7 +532,7 @@ int adj_impl(int lmax, int mbmax, int nring, const double* cosbeta, int npair, c
         if (!aligned16(Cbar[k])) return fail(TC_EINVAL, "complex arrays must be 16-byte aligned");
     }
     if (!any) return TC_OK;   // nothing requested
-    const tc::Tile t = default_tile(TC_OP_ADJ, lmax);
+    const tc::Tile t = call_tile(TC_OP_ADJ, lmax, count_slots(nring, cosbeta));
     const Layout L = make_layout(TC_OP_ADJ, lmax, mbmax, nring, cosbeta, t);
     if ((rc = check_ws(L, workspace, ws_bytes)) || (rc = check_grid(L))) return rc;
     rc = upload_tables(TC_OP_FWD, lmax, mbmax, nring, cosbeta, 0, nullptr, nullptr, L, t, workspace, stream,
@@ -1153,7 +1195,7 @@ int check_detector(int i, const tc_detector& d, int op, int lmax_sky)
 int walk_R(const tc::Tile& t, int nslot)
 {
     int R = t.R;
-    while (R > 2 && t.NT * (R / 2) >= nslot) R /= 2;
+    while (R > 2 && 256 * (R / 2) >= nslot) R /= 2;
     return R;
 }
 
@@ -1186,7 +1228,9 @@ std::vector<Walk> group_detectors(int op, int ndet, const tc_detector* dets,
     for (auto& c : cls) {
         std::stable_sort(c.begin(), c.end(), [&](int a, int b) { return dets[a].mbmax > dets[b].mbmax; });
         tc::Tile wt = t;
-        wt.R = walk_R(t, count_slots(dets[c[0]].nring, xr[c[0]].data()));
+        const int nslot = count_slots(dets[c[0]].nring, xr[c[0]].data());
+        wt.R = walk_R(t, nslot);
+        wt = fit_tile(op, wt, nslot);
         const size_t per_walk = (size_t)(op == TC_OP_FWD ? tc::fwd_walk_pairs(wt) : tc::adj_walk_pairs_of(wt));
         for (size_t k = 0; k < c.size(); k += per_walk)
             walks.push_back({std::vector<int>(c.begin() + k, c.begin() + std::min(c.size(), k + per_walk)), wt});
@@ -1273,7 +1317,7 @@ int tc_plan_create(void** plan, int op, int ndet, const tc_detector* dets, int l
     std::vector<tc::EpiArgs> ea(ndet);
     // Launch groups: the walks of one R (forward), of one R and one lmax (adjoint: each group's
     // epilogues run beside the next group's walks).
-    struct Group { int R, lmax; tc::Tile tile; long long cost; std::vector<int> walks; };
+    struct Group { int R, NT, lmax; tc::Tile tile; long long cost; std::vector<int> walks; };
     std::vector<Group> groups;
     struct Item { int grp, walk, col, tile; long long cost; };
     std::vector<Item> items;
@@ -1285,8 +1329,10 @@ int tc_plan_create(void** plan, int op, int ndet, const tc_detector* dets, int l
         const Layout& L = lay[w];
         const int glmax = op == TC_OP_ADJ ? d.lmax : -1;
         int grp = 0;
-        while (grp < (int)groups.size() && !(groups[grp].R == wt.R && groups[grp].lmax == glmax)) ++grp;
-        if (grp == (int)groups.size()) groups.push_back({wt.R, glmax, wt, 0, {}});
+        while (grp < (int)groups.size() &&
+               !(groups[grp].R == wt.R && groups[grp].NT == wt.NT && groups[grp].lmax == glmax))
+            ++grp;
+        if (grp == (int)groups.size()) groups.push_back({wt.R, wt.NT, glmax, wt, 0, {}});
         groups[grp].walks.push_back(w);
         std::vector<char> img(L.tables_end, 0);
         build_rings(d.nring, xr[mem[0]].data(), img, L);

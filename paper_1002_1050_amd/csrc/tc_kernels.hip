@@ -828,10 +828,12 @@ __device__ __forceinline__ void fwd_column_walk(const FwdArgs& a, int ci, int ti
     load_raw(l0 + tid);
     stage_raw(l0, true);
     const int n = L - l0 + 1;              // l values of a chain
+    // a wave beyond the last ring slot only stages
+    const bool idle = tile * (NT * R) + __builtin_amdgcn_readfirstlane(tid >> 6) * (64 * R) >= a.nslot;
     for (int b0 = 0; b0 < n; b0 += NT) {
         const bool more = b0 + NT < n;
         if (more) load_raw(l0 + b0 + NT + tid);     // in flight during the block
-        const int send = min(NT, n - b0);
+        const int send = idle ? 0 : min(NT, n - b0);
         for (int s1 = 0; s1 < send; s1 += RS_STEPS) {
             if (scaled) {
                 bool any = false;
@@ -1186,8 +1188,11 @@ __device__ __forceinline__ void adj_column(const AdjArgs& a, int ci, int tile, A
     __syncthreads();
     // lane 15 of a row finishes l = L at time n - 1 + SKEW; the last block runs whole step groups
     const int T = n + SKEW;
+    // waves beyond the last ring slot only stage and sum
+    const int nact = min(NW, (a.nslot - tile * (NT * R) + 64 * R - 1) / (64 * R));
+    const bool idle = __builtin_amdgcn_readfirstlane(wave) >= nact;
     for (int buf_t = 0; buf_t < T; buf_t += TB) {
-        const int send = min(TB, T - buf_t);
+        const int send = idle ? 0 : min(TB, T - buf_t);
         for (int s1 = 0; s1 < send; s1 += RS_STEPS) {
             if (scaled) {
                 bool any = false;
@@ -1289,7 +1294,12 @@ __device__ __forceinline__ void adj_column(const AdjArgs& a, int ci, int tile, A
                 const double* src = sh_.out + ((o - 1) & OUT_MASK) * OS + comp;
                 double v = 0.0;
 #pragma unroll
-                for (int w = 0; w < NW * 4; ++w) v += src[NS * w];
+                for (int w = 0; w < NW; ++w) {
+                    if (w < nact) {
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) v += src[NS * (4 * w + k)];
+                    }
+                }
                 v *= sh_.cic[o & CF_MASK];   // e^l back to d^l
                 const int c = comp >> 2, part = comp & 3;
                 // the cotangent's rows by selection: a runtime index into the argument
@@ -1319,10 +1329,10 @@ __device__ __forceinline__ void adj_tiles(const AdjArgs& a, int ci, AdjShared<NT
     }
 }
 
-template <int R, int NT, int TB, int TR>
+template <int R, int NT, int TB>
 __global__ void __launch_bounds__(NT, (adj_min_waves<R, TB>())) k_adj(const AdjArgs a)
 {
-    static_assert(adj_lds_bytes<NT, TB, 1>() * adj_min_waves<R, TB>() <= 160 * 1024, "LDS per CU");
+    static_assert(adj_lds_bytes<NT, TB, 1>() * adj_min_waves<R, TB>() * 256 / NT <= 160 * 1024, "LDS per CU");
     __shared__ AdjShared<NT, TB, 1> sh;
     adj_tiles<R, NT, TB, 1, 1>(a, blockIdx.x, sh);
 }
@@ -1342,12 +1352,12 @@ constexpr int adj_walk_pairs() { return (R <= 4 && TB <= 32) ? 2 : 1; }
 template <int R, int TB>
 constexpr int adj_items_min_waves() { return adj_walk_pairs<R, TB>() == 2 ? 2 : adj_min_waves<R, TB>(); }
 
-template <int R, int NT, int TB, int TR>
+template <int R, int NT, int TB>
 __global__ void __launch_bounds__(NT, (adj_items_min_waves<R, TB>())) k_adj_items(const AdjArgs* __restrict__ dets,
                                                                             const int* __restrict__ items)
 {
     constexpr int K = adj_walk_pairs<R, TB>();
-    static_assert(adj_lds_bytes<NT, TB, K>() * 2 <= 160 * 1024, "two workgroups per CU");
+    static_assert(adj_lds_bytes<NT, TB, K>() * (NT == 64 ? 7 : 512 / NT) <= 160 * 1024, "about two waves per SIMD");
     __shared__ AdjShared<NT, TB, K> sh;
     const int* item = items + 2 * (size_t)blockIdx.x;
     const int ci = item[1];
@@ -1494,17 +1504,18 @@ __global__ void __launch_bounds__(256) k_beam_symmetry(const double2* __restrict
 
 }  // namespace
 
-// Built tile variants.  Forward and adjoint: R in {2, 4, 8}, TB in {32, 64}, TR = 4.
-// Polarised forward (op 3): R in {2, 4}, TB in {32, 64}.  Wigner: R in {1, 4}, TB = 32.
+// Built tile variants (NT lanes per workgroup).  Forward: R in {2, 4, 8} (polarised: {2, 4}) with
+// NT in {64, 128, 256}; TB shapes no forward kernel (a block is NT values of l).  Adjoint: R in
+// {2, 4, 8}, TB 32 with each NT, TB 64 with NT 256.  Wigner: R in {1, 4}, NT 256, TB 32.
 bool tile_supported(int op, Tile t)
 {
-    if (t.NT != 256) return false;
-    if (op == 0) return (t.R == 1 || t.R == 4) && t.TB == 32;
-    const bool r_ok = t.R == 2 || t.R == 4 || t.R == 8;
+    const bool nt_ok = t.NT == 64 || t.NT == 128 || t.NT == 256;
     const bool tb_ok = t.TB == 32 || t.TB == 64;
-    if (op == 1) return r_ok && tb_ok;
-    if (op == 2) return r_ok && tb_ok && t.TR == 4;
-    if (op == 3) return (t.R == 2 || t.R == 4) && tb_ok;
+    const bool r_ok = t.R == 2 || t.R == 4 || t.R == 8;
+    if (op == 0) return (t.R == 1 || t.R == 4) && t.TB == 32 && t.NT == 256;
+    if (op == 1) return r_ok && tb_ok && nt_ok;
+    if (op == 2) return r_ok && tb_ok && t.TR == 4 && (t.NT == 256 || (nt_ok && t.TB == 32));
+    if (op == 3) return (t.R == 2 || t.R == 4) && tb_ok && nt_ok;
     return false;
 }
 
@@ -1518,10 +1529,15 @@ int launch_wigner(const WignerArgs& a, Tile t, void* stream)
     }
 }
 
-// Maps a runtime (R, TB[, TR]) onto the template instantiation F<R, TB[, TR]>.
-#define TC_FWD_VARIANTS(X) X(2) X(4) X(8)
-#define TC_FWDPOL_VARIANTS(X) X(2, 1, 2) X(4, 1, 2) X(2, 1, 3) X(4, 1, 3) X(2, 2, 2) X(4, 2, 2) X(2, 3, 3) X(4, 3, 3)
-#define TC_ADJ_VARIANTS(X) X(2, 32, 4) X(4, 32, 4) X(8, 32, 4) X(2, 64, 4) X(4, 64, 4) X(8, 64, 4)
+// Maps a runtime (R, NT[, TB]) onto the template instantiation F<R, NT[, TB]>.
+#define TC_NT(X, r) X(r, 64) X(r, 128) X(r, 256)
+#define TC_FWD_VARIANTS(X) TC_NT(X, 2) TC_NT(X, 4) TC_NT(X, 8)
+#define TC_NT_POL(X, r, c, p) X(r, 64, c, p) X(r, 128, c, p) X(r, 256, c, p)
+#define TC_FWDPOL_VARIANTS(X)                                                                  \
+    TC_NT_POL(X, 2, 1, 2) TC_NT_POL(X, 4, 1, 2) TC_NT_POL(X, 2, 1, 3) TC_NT_POL(X, 4, 1, 3)    \
+    TC_NT_POL(X, 2, 2, 2) TC_NT_POL(X, 4, 2, 2) TC_NT_POL(X, 2, 3, 3) TC_NT_POL(X, 4, 3, 3)
+#define TC_ADJ_NT(X, r) X(r, 64, 32) X(r, 128, 32) X(r, 256, 32) X(r, 256, 64)
+#define TC_ADJ_VARIANTS(X) TC_ADJ_NT(X, 2) TC_ADJ_NT(X, 4) TC_ADJ_NT(X, 8)
 
 int launch_beam_symmetry(const double* blm, int lmax, int mbmax, int* sym, void* stream)
 {
@@ -1534,22 +1550,22 @@ int launch_fwd(const FwdArgs& a, Tile t, void* stream)
 {
     const int blocks = a.ncol * a.ntile;
     if (a.npair == 1) {
-#define X(r)                                                                                  \
-    if (t.R == r) {                                                                           \
+#define X(r, nt)                                                                              \
+    if (t.R == r && t.NT == nt) {                                                             \
         if (a.beam_sym[0]) {                                                                  \
-            const int rc = launch_grid(k_fwd_rows<r, 256>, a, blocks, 256, stream);           \
+            const int rc = launch_grid(k_fwd_rows<r, nt>, a, blocks, nt, stream);             \
             if (rc) return rc;                                                                \
         }                                                                                     \
-        return launch_grid(k_fwd<r, 256, 1, 1>, a, blocks, 256, stream);                      \
+        return launch_grid(k_fwd<r, nt, 1, 1>, a, blocks, nt, stream);                        \
     }
         TC_FWD_VARIANTS(X)
 #undef X
         return (int)hipErrorInvalidValue;
     }
     const int nc = a.sum ? 1 : a.npair;
-#define X(r, c, p)                                             \
-    if (t.R == r && nc == c && a.npair == p)                   \
-        return launch_grid(k_fwd<r, 256, c, p>, a, blocks, 256, stream);
+#define X(r, nt, c, p)                                         \
+    if (t.R == r && t.NT == nt && nc == c && a.npair == p)     \
+        return launch_grid(k_fwd<r, nt, c, p>, a, blocks, nt, stream);
     TC_FWDPOL_VARIANTS(X)
 #undef X
     return (int)hipErrorInvalidValue;
@@ -1558,8 +1574,8 @@ int launch_fwd(const FwdArgs& a, Tile t, void* stream)
 int launch_adj(const AdjArgs& a, Tile t, void* stream)
 {
     const int blocks = a.ncol;   // every ring tile of a column in one workgroup
-#define X(r, tb, tr) \
-    if (t.R == r && t.TB == tb && t.TR == tr) return launch_grid(k_adj<r, 256, tb, tr>, a, blocks, 256, stream);
+#define X(r, nt, tb) \
+    if (t.R == r && t.NT == nt && t.TB == tb) return launch_grid(k_adj<r, nt, tb>, a, blocks, nt, stream);
     TC_ADJ_VARIANTS(X)
 #undef X
     return (int)hipErrorInvalidValue;
@@ -1590,9 +1606,9 @@ int launch_fwd_items(const FwdArgs* walks, const int* items, int nitems, Tile t,
 {
     if (nitems <= 0) return 0;
     hipStream_t s = (hipStream_t)stream;
-#define X(r)                                                                                             \
-    if (t.R == r) {                                                                                      \
-        hipLaunchKernelGGL((k_fwd_items<r, 256>), dim3(nitems), dim3(256), 0, s, walks, items);          \
+#define X(r, nt)                                                                                         \
+    if (t.R == r && t.NT == nt) {                                                                        \
+        hipLaunchKernelGGL((k_fwd_items<r, nt>), dim3(nitems), dim3(nt), 0, s, walks, items);            \
         return (int)hipGetLastError();                                                                   \
     }
     TC_FWD_VARIANTS(X)
@@ -1612,10 +1628,10 @@ int launch_adj_items(const AdjArgs* dets, const int* items, int nitems, Tile t, 
 {
     if (nitems <= 0) return 0;
     hipStream_t s = (hipStream_t)stream;
-#define X(r, tb, tr)                                                                                        \
-    if (t.R == r && t.TB == tb && t.TR == tr) {                                                             \
-        hipLaunchKernelGGL((k_adj_items<r, 256, tb, tr>), dim3(nitems), dim3(256), 0, s, dets, items);      \
-        return (int)hipGetLastError();                                                                      \
+#define X(r, nt, tb)                                                                                    \
+    if (t.R == r && t.NT == nt && t.TB == tb) {                                                         \
+        hipLaunchKernelGGL((k_adj_items<r, nt, tb>), dim3(nitems), dim3(nt), 0, s, dets, items);        \
+        return (int)hipGetLastError();                                                                  \
     }
     TC_ADJ_VARIANTS(X)
 #undef X

@@ -1,5 +1,6 @@
-"""Chains that end at, just before and just after a staged block of l (256 values), a look period
-(32) and an unrolled group (8), in the forward's two forms and the adjoint, against the oracle.
+"""Chains that end at, just before and just after a staged block of l (64, 128 or 256 values), a look
+period (32) and an unrolled group (8), and ring sets at the widths of the built workgroups, in the
+forward's two forms and the adjoint, against the oracle.
 
 Tolerance: each of a chain's n <= 514 steps rounds by a few ulp (1.1e-16) and an error of one step
 grows at most linearly in the oscillating range, so a column is off by less than a few n^2 ulp =
@@ -48,6 +49,30 @@ def test_chain_lengths_around_blocks(B, L, beam):
     print(f"[gpu] blocks L={L} beam={beam}", flush=True)
     C = B.totalconv_fwd_x(L, M, x, dev(alm_h), dev(blm_h)).cpu().numpy()
     assert column_error(C, oracle.totalconv_fwd(L, M, x, alm_h, blm_h)) <= TOL
+    ga, gb = B.totalconv_adj_x(L, M, x, dev(alm_h), dev(blm_h), dev(G_h))
+    ga_ref, gb_ref = oracle.totalconv_adj(L, M, x, alm_h, blm_h, G_h)
+    assert np.linalg.norm(ga.cpu().numpy() - ga_ref) <= TOL * np.linalg.norm(ga_ref)
+    for r in range(2 * M + 1):
+        assert np.linalg.norm(gb.cpu().numpy()[r] - gb_ref[r]) <= TOL * np.linalg.norm(gb_ref[r])
+
+
+@pytest.mark.parametrize("nslot", [1, 2, 63, 64, 65, 127, 129, 255, 257, 511, 513, 769, 1023, 1025, 1537, 2047, 2049])
+@pytest.mark.parametrize("beam", ["gauss", "complex"])
+def test_ring_slots_around_workgroups(B, nslot, beam):
+    """Ring slots at and beside the widths of the built workgroups (64 to 2048 slots): one tile, several,
+    tiles with idle waves; mirror pairs and, for odd ring counts, the single equator ring."""
+    import oracle
+    L, M = 24, 2
+    nring = 2 * nslot - (nslot & 1)
+    x = S.ring_cosines(nring)
+    alm_h = S.sky_alm(L, 21)
+    blm_h = S.beam_blm(L, M, 300.0, 0.2) if beam == "gauss" else S.random_beam(L, M, 22)
+    G_h = S.random_cbar(L, M, nring, 23)
+    print(f"[gpu] slots nslot={nslot} beam={beam}", flush=True)
+    C = B.totalconv_fwd_x(L, M, x, dev(alm_h), dev(blm_h)).cpu().numpy()
+    assert column_error(C, oracle.totalconv_fwd(L, M, x, alm_h, blm_h)) <= TOL
+    pol = B.totalconv_fwd_pol_x(L, M, x, [dev(alm_h)] * 2, [dev(blm_h), dev(2 * blm_h)])
+    assert column_error(pol[0].cpu().numpy(), C) <= TOL and column_error(pol[1].cpu().numpy(), 2 * C) <= TOL
     ga, gb = B.totalconv_adj_x(L, M, x, dev(alm_h), dev(blm_h), dev(G_h))
     ga_ref, gb_ref = oracle.totalconv_adj(L, M, x, alm_h, blm_h, G_h)
     assert np.linalg.norm(ga.cpu().numpy() - ga_ref) <= TOL * np.linalg.norm(ga_ref)
