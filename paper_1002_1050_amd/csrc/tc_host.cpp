@@ -560,6 +560,17 @@ int adj_impl(int lmax, int mbmax, int nring, const double* cosbeta, int npair, c
             need |= (alm_bar && alm_bar[p]) || (blm_bar && blm_bar[p]);
         if (!need) continue;
         a.Cbar[0] = Cbar[k];
+        // The sky gradient of one pair alone: with the row signs of its beam, a column whose rows are
+        // related by one forms one sum instead of two.  The signs (2 mbmax + 1 ints) lie in front of V:
+        // the first mbmax complex values of its row mb = -mbmax are those of l < mbmax at msky = 0, which
+        // no column writes and no epilogue reads.
+        a.beam_sym = nullptr;
+        if (p1 - p0 == 1 && mbmax >= 1 && !(blm_bar && blm_bar[p0])) {
+            int* sym = reinterpret_cast<int*>(a.V[0]);
+            if ((rc = tc::launch_beam_symmetry(blm[p0], lmax, mbmax, sym, stream)))
+                return hip_fail(rc, "beam symmetry launch");
+            a.beam_sym = sym;
+        }
         // one workgroup per column walks its ring tiles in order: tile 0 writes U and V, later tiles add
         rc = timed_launch(TC_OP_ADJ, stream, [&] { return tc::launch_adj(a, t, stream); });
         if (rc) return hip_fail(rc, "totalconv_adj launch");
@@ -584,6 +595,7 @@ int adj_impl(int lmax, int mbmax, int nring, const double* cosbeta, int npair, c
             e.U = a.U[0]; e.V = a.V[0]; e.alm = alm[p]; e.blm = blm[p];
             e.alm_bar = (alm_bar && !sky_shared) ? alm_bar[p] : nullptr;
             e.blm_bar = blm_bar ? blm_bar[p] : nullptr;
+            e.beam_sym = a.beam_sym;
             if ((rc = tc::launch_adj_epilogue(e, stream))) return hip_fail(rc, "totalconv_adj epilogue launch");
         }
     }

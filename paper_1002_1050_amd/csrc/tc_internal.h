@@ -76,6 +76,8 @@ struct AdjArgs {
     double* U[kMaxPairs];  // complex [2 pmbmax+1][P] direct-ring sums u_l (all ring tiles of a column)
     double* V[kMaxPairs];  // complex [2 pmbmax+1][P] mirror-ring sums (before the (-1)^(l-msky) sign)
     long long P;           // (L+1)(L+2)/2
+    const int* beam_sym;   // sky gradient alone, one cotangent: its beam's row signs (as FwdArgs::beam_sym);
+                           // a column whose rows are related by a sign then forms one sum, in U.  Else null
 };
 
 struct EpiArgs {
@@ -88,6 +90,7 @@ struct EpiArgs {
     const double* blm;
     double* alm_bar;       // may be null
     double* blm_bar;       // may be null
+    const int* beam_sym;   // AdjArgs::beam_sym: rows with a sign hold their whole sum in U; V is not read
 };
 
 // The sky gradients of npair (2 or 3) (sky, beam) pairs that share one cotangent and so one U, V

@@ -896,10 +896,24 @@ __device__ __forceinline__ void fwd_column_walk(const FwdArgs& a, int ci, int ti
     }
 }
 
-// Beam row sign of pair p for row mb (0: the rows are not related by a sign).
+// The sign by which the walks take beam rows mb and -mb as related, from the signs sym of the rows
+// -mbmax .. mbmax (0: not related).  Row 0 equals itself, so its column could always take the shorter
+// form; where no other rows are related it is left with the others: alone in the launch of the short
+// form its lmax + 1 workgroups last as long as the longest chain (forward of a complex beam at lmax
+// 260: 30 of 100 us).
+__device__ __forceinline__ int related_sign(const int* sym, int mbmax, int mb)
+{
+    const int s = ldg(sym + mb + mbmax);
+    if (mb != 0 || mbmax == 0) return s;
+    int any = 0;
+    for (int m = 1; m <= mbmax; ++m) any |= ldg(sym + m + mbmax);
+    return any ? s : 0;
+}
+
+// The same for pair p of the forward.
 __device__ __forceinline__ int row_sign(const FwdArgs& a, int p, int mb)
 {
-    return ldg(a.beam_sym[p] + mb + a.pmbmax[p]);
+    return related_sign(a.beam_sym[p], a.pmbmax[p], mb);
 }
 
 // The scalar forward runs as two launches over every (column, tile): k_fwd_rows takes the
@@ -925,6 +939,22 @@ __global__ void __launch_bounds__(NT, (rows_min_waves<R>())) k_fwd_rows(const Fw
     const int s[1] = {row_sign(a, 0, ldg(a.col.mb + ci))};
     if (s[0] == 0) return;
     fwd_column_walk<R, NT, 1, 1, true, 0>(a, ci, blockIdx.x - ci * a.ntile, s, sh);
+}
+
+// Both forms in one launch, for the workgroups of small ring sets (NT < 256), whose calls last not much
+// longer than a launch (lmax 64: 48 -> 43 us a call, lmax 500: 248 -> 243 us).  At NT 256, R 8 the two
+// forms in one kernel cost the even / odd one 2%, so there each has its launch.
+template <int R, int NT>
+__global__ void __launch_bounds__(NT, (rows_min_waves<R>() < fwd_min_waves<R, 1, 1>() ? rows_min_waves<R>() : fwd_min_waves<R, 1, 1>()))
+k_fwd_either(const FwdArgs a)
+{
+    __shared__ FwdShared<NT, coef_slots<1, false>()> sh;
+    const int ci = blockIdx.x / a.ntile, tile = blockIdx.x - ci * a.ntile;
+    const int s[1] = {row_sign(a, 0, ldg(a.col.mb + ci))};
+    if (s[0] != 0)
+        fwd_column_walk<R, NT, 1, 1, true, 0>(a, ci, tile, s, sh);
+    else
+        fwd_column_walk<R, NT, 1, 1, false, 0>(a, ci, tile, s, sh);
 }
 
 // Batched form: one workgroup per (walk, column, ring tile) item, the items in order of cost,
@@ -1020,43 +1050,53 @@ __device__ __forceinline__ double row_shift_up(double v)
     return __hiloint2double(hi, lo);
 }
 
+// The sky gradient alone (SKY).  Column mb adds b_{l,mb} U_l + (-1)^(l-msky) b_{l,-mb} V_l to sky_bar_l;
+// where the beam's rows are related by a sign, b_{l,-mb} = s b_{l,mb}, that is b_{l,mb} times the one sum
+// sum_j d^l (Cbar_j + s (-1)^(l-msky) Cbar_{-mb,msky}(pi - beta_j)).  A lane holds the two
+// combinations of its chains' cotangents, one for its even and one for its odd row times, and a step
+// takes 2 + 2 instead of 2 + 4 multiply-adds per chain and shifts one complex sum instead of two.
+// Sky gradient of 1001 slots at lmax 1023: 2.20 -> 1.66 ms, of 2048 at lmax 2048 22.7 -> 17.6 ms.
+
 // Emitted row sums: slot (t - 16) mod 2 TB for the sum that leaves lane 15 at time t
 // (l offset t - 15), then (wave, row, component); slots are out_stride doubles apart: two more
-// than the NW 4 4 NC they hold, an even count, so that every slot is 16-byte aligned and a step
+// than the NW 4 NS they hold, an even count, so that every slot is 16-byte aligned and a step
 // group's emissions are 128-bit stores at constant offsets from one address (the reads of the
-// block sum, one slot per lane, then meet at most two to a bank).  NC cotangents share the walk:
-// 4 NC components.
-template <int NT, int NC>
-constexpr int out_stride() { return (NT / 64) * 4 * 4 * NC + 2; }
+// block sum, one slot per lane, then meet at most two to a bank).  NS components: 4 per cotangent of
+// the walk, 2 for the sky gradient alone.
+template <int NT, int NS>
+constexpr int out_stride() { return (NT / 64) * 4 * NS + 2; }
 
 // The coefficient ring holds the last two staged blocks of NT l offsets plus a copy of its first
 // TS slots behind its end, so that the TS consecutive offsets of a step group never wrap.
-// NCMAX: the most cotangents a walk in this workgroup serves.
-template <int NT, int TB, int NCMAX>
+// NSMAX: the most components a walk in this workgroup sums.
+template <int NT, int TB, int NSMAX>
 struct AdjShared {
     double2 cfa[2 * NT + TS];                     // {A', nB'} per l offset, slot = offset mod 2 NT
     double cic[2 * NT];                           // 1 / c_l per l offset
-    double out[2 * TB * out_stride<NT, NCMAX>()]; // emitted row sums
+    double out[2 * TB * out_stride<NT, NSMAX>()]; // emitted row sums
     NormShared<NT> norm;
     int grow[2 * NT / RS_STEPS];                  // growth bounds, slot = offset / RS_STEPS mod 2 NT / RS_STEPS
 };
 
-template <int NT, int TB, int NCMAX>
-constexpr size_t adj_lds_bytes() { return sizeof(AdjShared<NT, TB, NCMAX>); }
+template <int NT, int TB, int NSMAX>
+constexpr size_t adj_lds_bytes() { return sizeof(AdjShared<NT, TB, NSMAX>); }
 
 // One ring tile of column ci for the cotangents 0 .. NC - 1 of the walk (a.Cbar[c], sums into
-// a.U[c], a.V[c], rows of cotangent c offset by a.pmbmax[c]).
-template <int R, int NT, int TB, int NC, int NCMAX>
-__device__ __forceinline__ void adj_column(const AdjArgs& a, int ci, int tile, AdjShared<NT, TB, NCMAX>& sh_)
+// a.U[c], a.V[c], rows of cotangent c offset by a.pmbmax[c]).  SKY: the sky gradient alone of one
+// cotangent on a column whose beam rows are related by the sign sky_sign, its one sum into a.U[0].
+template <int R, int NT, int TB, int NC, bool SKY, int NSMAX>
+__device__ __forceinline__ void adj_column(const AdjArgs& a, int ci, int tile, int sky_sign,
+                                           AdjShared<NT, TB, NSMAX>& sh_)
 {
     static_assert(TB % RS_STEPS == 0 && NT % TB == 0 && TS % 2 == 0 && TB >= ROW, "step groups: pairs of steps, TS per check");
-    static_assert(NC <= NCMAX && NC <= kMaxPairs, "cotangents per walk");
+    static_assert(NC <= kMaxPairs && (!SKY || NC == 1), "cotangents per walk");
     constexpr int NW = NT / 64;
-    constexpr int NS = 4 * NC;              // running sums per lane: (U re, U im, V re, V im) per cotangent
+    constexpr int NS = SKY ? 2 : 4 * NC;    // running sums per lane: (U re, U im, V re, V im) per cotangent
+    static_assert(NS <= NSMAX, "emitted components");
     constexpr int CF_N = 2 * NT;            // coefficient ring: the staged block of NT offsets and the one before
     constexpr int CF_MASK = CF_N - 1;
     constexpr int OUT_MASK = 2 * TB - 1;    // emitted sums: windows kb (written) and kb-1 (summed)
-    constexpr int OS = out_stride<NT, NC>();
+    constexpr int OS = out_stride<NT, NS>();
     static_assert((CF_N & CF_MASK) == 0 && (2 * TB & OUT_MASK) == 0 && (SKEW + 1) % TS == 0, "ring sizes");
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
@@ -1101,6 +1141,12 @@ __device__ __forceinline__ void adj_column(const AdjArgs& a, int ci, int tile, A
                 if (jm >= 0) {
                     const double2 v2 = ldg(Cbar + row_m + jm);
                     g2r[c][r] = v2.x; g2i[c][r] = v2.y;
+                }
+                if constexpr (SKY) {   // g1, g2: the combinations at even and at odd row times
+                    const double sg = ((l0 - ms + kr) & 1) ? -(double)sky_sign : (double)sky_sign;
+                    const double mr = sg * g2r[c][r], mi = sg * g2i[c][r];
+                    g2r[c][r] = g1r[c][r] - mr; g2i[c][r] = g1i[c][r] - mi;
+                    g1r[c][r] += mr; g1i[c][r] += mi;
                 }
             }
         }
@@ -1166,17 +1212,26 @@ __device__ __forceinline__ void adj_column(const AdjArgs& a, int ci, int tile, A
 #pragma unroll
         for (int q = 0; q < NS; ++q) sa[q] = row_shift_up(sb[q]);
     };
-    // one step of the R chains of this lane: coefficients k; the sums s take e * Cbar
-    auto step = [&](const double2 k, double (&s)[NS]) {
+    // the sums s take e * Cbar of chain r; odd: an odd row time (SKY)
+    auto add = [&](double dd, int r, double (&s)[NS], bool odd) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            if constexpr (SKY) {
+                s[0] = fma(dd, odd ? g2r[c][r] : g1r[c][r], s[0]);
+                s[1] = fma(dd, odd ? g2i[c][r] : g1i[c][r], s[1]);
+            } else {
+                s[4 * c + 0] = fma(dd, g1r[c][r], s[4 * c + 0]);
+                s[4 * c + 1] = fma(dd, g1i[c][r], s[4 * c + 1]);
+                s[4 * c + 2] = fma(dd, g2r[c][r], s[4 * c + 2]);
+                s[4 * c + 3] = fma(dd, g2i[c][r], s[4 * c + 3]);
+            }
+        }
+    };
+    // one step of the R chains of this lane: coefficients k
+    auto step = [&](const double2 k, double (&s)[NS], bool odd) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-#pragma unroll
-            for (int c = 0; c < NC; ++c) {
-                s[4 * c + 0] = fma(d[r], g1r[c][r], s[4 * c + 0]);
-                s[4 * c + 1] = fma(d[r], g1i[c][r], s[4 * c + 1]);
-                s[4 * c + 2] = fma(d[r], g2r[c][r], s[4 * c + 2]);
-                s[4 * c + 3] = fma(d[r], g2i[c][r], s[4 * c + 3]);
-            }
+            add(d[r], r, s, odd);
             const double u = fma(x[r], k.x, k.y);
             const double dn = fma(u, d[r], -dp[r]);
             dp[r] = d[r];
@@ -1229,14 +1284,8 @@ __device__ __forceinline__ void adj_column(const AdjArgs& a, int ci, int tile, A
 #pragma unroll
                         for (int r = 0; r < R; ++r) {
                             const double dd = (live && acc_on) ? d[r] : 0.0;
-#pragma unroll
-                            for (int c = 0; c < NC; ++c) {
-                                double* s = (t & 1) ? sa : sb;
-                                s[4 * c + 0] = fma(dd, g1r[c][r], s[4 * c + 0]);
-                                s[4 * c + 1] = fma(dd, g1i[c][r], s[4 * c + 1]);
-                                s[4 * c + 2] = fma(dd, g2r[c][r], s[4 * c + 2]);
-                                s[4 * c + 3] = fma(dd, g2i[c][r], s[4 * c + 3]);
-                            }
+                            if (t & 1) add(dd, r, sa, true);
+                            else add(dd, r, sb, false);
                             const double u = fma(x[r], k.x, k.y);
                             const double dn = fma(u, d[r], -dp[r]);
                             dp[r] = live ? d[r] : dp[r];
@@ -1256,9 +1305,9 @@ __device__ __forceinline__ void adj_column(const AdjArgs& a, int ci, int tile, A
                             kn0 = sh_.cfa[cb + h + 2]; kn1 = sh_.cfa[cb + h + 3];
                         }
                         shift_a_to_b();
-                        step(k0, sb);
+                        step(k0, sb, false);
                         shift_b_to_a();
-                        step(k1, sa);
+                        step(k1, sa, true);
                         emit2_in(og, h);
                     }
                 } else {
@@ -1301,7 +1350,7 @@ __device__ __forceinline__ void adj_column(const AdjArgs& a, int ci, int tile, A
                     }
                 }
                 v *= sh_.cic[o & CF_MASK];   // e^l back to d^l
-                const int c = comp >> 2, part = comp & 3;
+                const int c = SKY ? 0 : comp >> 2, part = comp & 3;
                 // the cotangent's rows by selection: a runtime index into the argument
                 // record would move the record to scratch memory
                 double* uv = part < 2 ? a.U[0] : a.V[0];
@@ -1320,21 +1369,41 @@ __device__ __forceinline__ void adj_column(const AdjArgs& a, int ci, int tile, A
 // column's U and V rows, each later tile adds to them (the same thread writes an element in
 // every tile), so no launch has to wait for another.  The column's values the compiler keeps
 // across tiles spill outside the step loops only.
-template <int R, int NT, int TB, int NC, int NCMAX>
-__device__ __forceinline__ void adj_tiles(const AdjArgs& a, int ci, AdjShared<NT, TB, NCMAX>& sh)
+template <int R, int NT, int TB, int NC, bool SKY, int NSMAX>
+__device__ __forceinline__ void adj_tiles(const AdjArgs& a, int ci, int sky_sign, AdjShared<NT, TB, NSMAX>& sh)
 {
     for (int tile = 0; tile < a.ntile; ++tile) {
         if (tile > 0) __syncthreads();   // the tile before still reads the LDS ring in its last block sums
-        adj_column<R, NT, TB, NC, NCMAX>(a, ci, tile, sh);
+        adj_column<R, NT, TB, NC, SKY, NSMAX>(a, ci, tile, sky_sign, sh);
     }
 }
 
 template <int R, int NT, int TB>
 __global__ void __launch_bounds__(NT, (adj_min_waves<R, TB>())) k_adj(const AdjArgs a)
 {
-    static_assert(adj_lds_bytes<NT, TB, 1>() * adj_min_waves<R, TB>() * 256 / NT <= 160 * 1024, "LDS per CU");
-    __shared__ AdjShared<NT, TB, 1> sh;
-    adj_tiles<R, NT, TB, 1, 1>(a, blockIdx.x, sh);
+    static_assert(adj_lds_bytes<NT, TB, 4>() * adj_min_waves<R, TB>() * 256 / NT <= 160 * 1024, "LDS per CU");
+    __shared__ AdjShared<NT, TB, 4> sh;
+    if (a.beam_sym && related_sign(a.beam_sym, a.pmbmax[0], ldg(a.col.mb + blockIdx.x)) != 0) return;   // k_adj_one_sum's
+    adj_tiles<R, NT, TB, 1, false, 4>(a, blockIdx.x, 0, sh);
+}
+
+// The columns whose beam rows are related by a sign, for the sky gradient alone.
+template <int R, int NT, int TB>
+__global__ void __launch_bounds__(NT, (adj_min_waves<R, TB>())) k_adj_one_sum(const AdjArgs a)
+{
+    __shared__ AdjShared<NT, TB, 2> sh;
+    const int s = related_sign(a.beam_sym, a.pmbmax[0], ldg(a.col.mb + blockIdx.x));
+    if (s != 0) adj_tiles<R, NT, TB, 1, true, 2>(a, blockIdx.x, s, sh);
+}
+
+// Both in one launch, for the workgroups of small ring sets (NT < 256).
+template <int R, int NT, int TB>
+__global__ void __launch_bounds__(NT, (adj_min_waves<R, TB>())) k_adj_either(const AdjArgs a)
+{
+    __shared__ AdjShared<NT, TB, 4> sh;
+    const int s = related_sign(a.beam_sym, a.pmbmax[0], ldg(a.col.mb + blockIdx.x));
+    if (s != 0) adj_tiles<R, NT, TB, 1, true, 4>(a, blockIdx.x, s, sh);
+    else adj_tiles<R, NT, TB, 1, false, 4>(a, blockIdx.x, 0, sh);
 }
 
 // Batched form: one workgroup per (walk, column) item, the items longest first.  A walk serves
@@ -1357,20 +1426,20 @@ __global__ void __launch_bounds__(NT, (adj_items_min_waves<R, TB>())) k_adj_item
                                                                             const int* __restrict__ items)
 {
     constexpr int K = adj_walk_pairs<R, TB>();
-    static_assert(adj_lds_bytes<NT, TB, K>() * (NT == 64 ? 7 : 512 / NT) <= 160 * 1024, "about two waves per SIMD");
-    __shared__ AdjShared<NT, TB, K> sh;
+    static_assert(adj_lds_bytes<NT, TB, 4 * K>() * (NT == 64 ? 7 : 512 / NT) <= 160 * 1024, "about two waves per SIMD");
+    __shared__ AdjShared<NT, TB, 4 * K> sh;
     const int* item = items + 2 * (size_t)blockIdx.x;
     const int ci = item[1];
     if constexpr (K == 2) {
         // read in place: a copy of the record would sit in scratch memory in this form
         const AdjArgs& a = dets[item[0]];
         if (a.npair > 1 && a.pmbmax[1] >= abs(ldg(a.col.mb + ci)))
-            adj_tiles<R, NT, TB, 2, K>(a, ci, sh);
+            adj_tiles<R, NT, TB, 2, false, 4 * K>(a, ci, 0, sh);
         else
-            adj_tiles<R, NT, TB, 1, K>(a, ci, sh);
+            adj_tiles<R, NT, TB, 1, false, 4 * K>(a, ci, 0, sh);
     } else {
         const AdjArgs a = dets[item[0]];
-        adj_tiles<R, NT, TB, 1, K>(a, ci, sh);
+        adj_tiles<R, NT, TB, 1, false, 4 * K>(a, ci, 0, sh);
     }
 }
 
@@ -1395,13 +1464,15 @@ __device__ __forceinline__ void sky_grad_terms(const EpiArgs& e, int ms, int l, 
     const double2* blm = reinterpret_cast<const double2*>(e.blm) + l;
     const int M = e.mbmax, lo = max(-M, -l), hi = min(M, l);   // rows with l >= |mb|
     const double sg = ((l - ms) & 1) ? -1.0 : 1.0;
+    const int* one_sum = e.beam_sym;
     for (int mb0 = lo; mb0 <= hi; mb0 += SKY_ROWS) {
         double2 ua[SKY_ROWS], va[SKY_ROWS], ba[SKY_ROWS];
 #pragma unroll
         for (int q = 0; q < SKY_ROWS; ++q) {
             const int mb = min(mb0 + q, hi);   // past the last row: a repeat of it, not added
             ua[q] = ldg(U + (size_t)(mb + M) * e.P);
-            va[q] = ldg(V + (size_t)(-mb + M) * e.P);
+            if (!one_sum || related_sign(one_sum, M, mb) == 0) va[q] = ldg(V + (size_t)(-mb + M) * e.P);
+            else va[q] = make_double2(0.0, 0.0);
             ba[q] = ldg(blm + (size_t)(mb + M) * (e.lmax + 1));
         }
 #pragma unroll
@@ -1552,6 +1623,8 @@ int launch_fwd(const FwdArgs& a, Tile t, void* stream)
     if (a.npair == 1) {
 #define X(r, nt)                                                                              \
     if (t.R == r && t.NT == nt) {                                                             \
+        if constexpr (nt < 256)                                                               \
+            if (a.beam_sym[0]) return launch_grid(k_fwd_either<r, nt>, a, blocks, nt, stream); \
         if (a.beam_sym[0]) {                                                                  \
             const int rc = launch_grid(k_fwd_rows<r, nt>, a, blocks, nt, stream);             \
             if (rc) return rc;                                                                \
@@ -1574,8 +1647,16 @@ int launch_fwd(const FwdArgs& a, Tile t, void* stream)
 int launch_adj(const AdjArgs& a, Tile t, void* stream)
 {
     const int blocks = a.ncol;   // every ring tile of a column in one workgroup
-#define X(r, nt, tb) \
-    if (t.R == r && t.NT == nt && t.TB == tb) return launch_grid(k_adj<r, nt, tb>, a, blocks, nt, stream);
+#define X(r, nt, tb)                                                                          \
+    if (t.R == r && t.NT == nt && t.TB == tb) {                                               \
+        if constexpr (nt < 256)                                                               \
+            if (a.beam_sym) return launch_grid(k_adj_either<r, nt, tb>, a, blocks, nt, stream); \
+        if (a.beam_sym) {                                                                     \
+            const int rc = launch_grid(k_adj_one_sum<r, nt, tb>, a, blocks, nt, stream);      \
+            if (rc) return rc;                                                                \
+        }                                                                                     \
+        return launch_grid(k_adj<r, nt, tb>, a, blocks, nt, stream);                          \
+    }
     TC_ADJ_VARIANTS(X)
 #undef X
     return (int)hipErrorInvalidValue;
