@@ -967,7 +967,8 @@ int wigner_d_rings_x(int lmax, int npair, const int* mb, const int* msky, int nr
     int rc = check_rings(nring, cosbeta);
     if (rc) return rc;
     if (!d) return fail(TC_EINVAL, "d is NULL");
-    const tc::Tile t = default_tile(TC_OP_WIGNER, lmax);
+    tc::Tile t = default_tile(TC_OP_WIGNER, lmax);
+    t.R = 1; t.NT = 128;   // the one built shape: a ring per lane
     const Layout L = make_layout(TC_OP_WIGNER, lmax, npair, nring, cosbeta, t);
     if ((rc = check_ws(L, workspace, ws_bytes)) || (rc = check_grid(L))) return rc;
     rc = upload_tables(TC_OP_WIGNER, lmax, npair, nring, cosbeta, npair, mb, msky, L, t, workspace, stream,

@@ -8,9 +8,8 @@
 // A lane takes R consecutive slots and a wave 64 R (slots run from the pole to
 // the equator), so that the chains of a wave share their regime: all still below
 // the skip threshold, or not, over the same stretch of l.
-// They are built per block of TB values of l in LDS (double-buffered: the next
-// block is prepared while the current one is consumed) and read back as
-// broadcasts.  A ring slot is either a mirror pair (beta, pi - beta) -- one
+// They are built per block of NT values of l in LDS by the whole workgroup and read
+// back as broadcasts.  A ring slot is either a mirror pair (beta, pi - beta) -- one
 // recursion serves both rings through d^l_{-mb,msky}(pi-beta) =
 // (-1)^(l-msky) d^l_{mb,msky}(beta) (appendix eq. pithetasym) -- or a single ring.
 //
@@ -29,9 +28,9 @@
 namespace tc {
 namespace {
 
-// Tile parameters (template arguments): R chains per lane, NT lanes per workgroup,
-// TB values of l per coefficient block; TR is kept in the tile triple (value 4) and no
-// longer shapes any kernel: the adjoint's row sums move every step.
+// Tile parameters (template arguments): R chains per lane, NT lanes per workgroup, TB
+// row times per block of the adjoint's emitted sums (the forward ignores it); TR is kept in the
+// tile triple (value 4) and shapes no kernel: the adjoint's row sums move every step.
 constexpr int TS = 8;         // steps per unrolled group
 constexpr int FOLD_EXP = -900;  // fold scaled values into plain doubles at 2^-900
 // A step of the normalised walk (below) multiplies max(|e^l|, |e^{l-1}|) by at most
@@ -178,32 +177,6 @@ __device__ __forceinline__ void seed_value(double lnAh, double lnAl, SeedShape s
     if (sh.neg) d = -d;
 }
 
-// ------------------------------------------------------ recursion coefficients
-// d^{l+1} = F0_l (x - F1_l) d^l - F2_l d^{l-1}  (Sec. 4.2.2), evaluated as
-// fma(x, A, nB) * d^l - F2 d^{l-1} with A = F0, nB = -F0 F1.  F0 and F2 come from
-// their closed forms; at l = lmax (and beyond) the step is switched off.
-__device__ __forceinline__ void recursion_coefs(int l, int mb, int ms, int lmax,
-                                                double& A, double& nB, double& F2)
-{
-    if (l >= lmax) {
-        A = 0.0; nB = 0.0; F2 = 0.0;
-        return;
-    }
-    const double l1 = (double)(l + 1);
-    const double b2 = (double)mb * (double)mb, s2 = (double)ms * (double)ms;
-    const double den = sqrt(l1 * l1 - b2) * sqrt(l1 * l1 - s2);
-    A = l1 * (2.0 * (double)l + 1.0) / den;
-    if (l == 0) {           // F1_0 = F2_0 = 0 (only the (0,0) chain reaches l = 0)
-        nB = 0.0;
-        F2 = 0.0;
-        return;
-    }
-    const double ll = (double)l;
-    const double F1 = ((double)mb * (double)ms) / (ll * l1);
-    nB = -(A * F1);
-    F2 = (l1 * (sqrt(ll * ll - b2) * sqrt(ll * ll - s2))) / (ll * den);
-}
-
 // ------------------------------------------------------------ normalised walk
 // The walks carry e^l = c_l d^l with c_{l0} = c_{l0+1} = 1 and c_{l+1} = c_{l-1} / F2_l.
 // The step then reads e^{l+1} = alpha_l F0 (x - F1) e^l - e^{l-1} with alpha_l = c_{l+1} / c_l:
@@ -220,57 +193,21 @@ struct NormCoef {
     double ic;      // 1 / c_l
 };
 
-// Coefficients of l = lb + lane for one block of TB values of l, computed by all 64 lanes of
-// one wave (the lanes past TB only take part in the scans).  carry holds c_{lb-2}, c_{lb-1}
-// (ignored for the first block, whose carry is 1, 1) and is replaced by c_{lb+TB-2}, c_{lb+TB-1}.
-// c_l is a product over segments of NORM_SEG values of l, each taking the last two c of the one
-// before, so it rounds the same way for every TB (plans and plain calls agree bit for bit).
-constexpr int NORM_SEG = 32;
-
-template <int TB>
-__device__ __forceinline__ NormCoef norm_coefs(int lb, int l0, int mb, int ms, int lmax, bool first, double* carry)
-{
-    static_assert(TB <= 64 && TB % NORM_SEG == 0, "one wave, whole segments");
-    const int i = threadIdx.x & 63;
-    const int l = lb + i;
-    double A, nB, F2;
-    recursion_coefs(l, mb, ms, lmax, A, nB, F2);
-    double m = 1.0;   // c_l / c_{l-2}
-    if (l >= l0 + 2 && l <= lmax) {
-        double A1, nB1, F2m;
-        recursion_coefs(l - 1, mb, ms, lmax, A1, nB1, F2m);
-        m = 1.0 / F2m;
-    }
-    double c = m;     // products over the lanes of one parity within the segment: offsets 2 .. 16
-    const int j = i & (NORM_SEG - 1);
-#pragma unroll
-    for (int off = 2; off < NORM_SEG; off *= 2) {
-        const double v = __shfl_up(c, off, 64);
-        if (j >= off) c *= v;
-    }
-    if (i < NORM_SEG) c *= (i & 1) ? (first ? 1.0 : carry[1]) : (first ? 1.0 : carry[0]);
-    const double s_even = __shfl(c, NORM_SEG - 2, 64), s_odd = __shfl(c, NORM_SEG - 1, 64);
-    if (i >= NORM_SEG) c *= (i & 1) ? s_odd : s_even;
-    const double c_up = __shfl_up(c, 1, 64);
-    double c_next = __shfl_down(c, 1, 64);                      // c_{l+1}
-    if (i == 63) c_next = (l < lmax) ? (1.0 / F2) * c_up : c_up;  // as the next block's first lane
-    const double alpha = c_next / c;
-    if (i == TB - 2) carry[0] = c;
-    if (i == TB - 1) carry[1] = c;
-    return NormCoef{alpha * A, alpha * nB, 1.0 / c};
-}
-
-// The same coefficients staged by the whole workgroup: lane tid takes l = lb + tid, so a block
-// is NT values of l and every wave stages 64 of them.  (With one wave staging a block of 64 while
-// the others wait at the barrier, the staging wave's SIMD is late in every block.)
+// Coefficients of one block of NT values of l, staged by the whole workgroup: lane tid takes l =
+// lb + tid, so every wave stages 64 of them.  (With one wave staging a block of 64 while the others
+// wait at the barrier, the staging wave's SIMD is late in every block.)  c_l is a product over
+// segments of NORM_SEG values of l, each taking the last two c of the one before in order, so it
+// rounds the same way for every NT.
 //
 // With S(l) = sqrt((l^2 - mb^2)(l^2 - msky^2)) the closed forms are F0_l = (l+1)(2l+1) / S(l+1) and
 // F2_l = (l+1) S(l) / (l S(l+1)), so c_l / c_{l-2} = (l-1) S(l) / (l S(l-1)).  A lane takes the root at
 // l + 1 and its reciprocal by a joint iteration and gets those at l from its neighbour; the
 // quotients come from these reciprocals with one correction, to within rounding of the correctly
 // rounded ones.  (Products with the reciprocals alone, uncorrected, were 0.5% faster at lmax 4096
-// and doubled the error of C and of the gradients.)  About a third of norm_coefs's operations,
-// with one root in place of eight.
+// and doubled the error of C and of the gradients.)  About 150 VALU operations per wave and 64
+// values of l, where four roots and four divisions at each of l and l - 1 took about 350.
+constexpr int NORM_SEG = 32;
+
 template <int NT>
 struct NormShared {
     double edge[NT / 64 + 1][3];   // S(l+1), 1/S(l+1), c_{l+1} / c_{l-1} of a wave's last l; [0]: of the block before
@@ -401,17 +338,6 @@ __device__ __forceinline__ NormCoef norm_coefs_group(int lb, int l0, int mb, int
     return NormCoef{alpha * A, alpha * nB, ic};
 }
 
-// Binary exponent e of max(|d|, |d_prev|) (|v| in [2^(e-1), 2^e)); a zero value does
-// not count (the caller treats d = d_prev = 0 as the zero chain).
-__device__ __forceinline__ int chain_exponent(double d, double dp)
-{
-    int e1, e2;
-    frexp(d, &e1);
-    frexp(dp, &e2);
-    constexpr int NONE = -(1 << 20);
-    return max(d != 0.0 ? e1 : NONE, dp != 0.0 ? e2 : NONE);
-}
-
 // The skip test of a wave's plain chains (E = 0): whether any may reach 2^-skip_exp within the next
 // RS_STEPS steps, each of which grows max(|d|, |d_prev|) by at most 2^bits.  Only high words are
 // compared (the threshold is a power of two): three integer operations a chain, where the maxima
@@ -432,24 +358,6 @@ __device__ __forceinline__ bool wave_may_be_hot(const double (&d)[R], const doub
     return wave_any(m >= (unsigned)(1023 - skip_exp - bits * RS_STEPS) << 20);
 }
 
-// One scale check of a chain where each d is written out (every TS steps).  From the exponent e of
-// max(|d|, |d_prev|) it takes the true exponent te = E + e of the chain.
-//  - rescale: a scaled chain (E < 0) is folded into plain doubles once te reaches
-//    -900 (k = E), otherwise brought back to a significand near 1 (k = -e).
-// Branch-free per chain; the callers' conditions are wave-uniform.
-__device__ __forceinline__ void check_chain(double& d, double& dp, int& E)
-{
-    const bool nz = (d != 0.0) | (dp != 0.0);
-    const int e = chain_exponent(d, dp);
-    const int te = E + e;
-    const bool sc = nz & (E < 0);
-    const bool fold = te >= FOLD_EXP;
-    const int k = sc ? (fold ? E : -e) : 0;
-    E = sc ? (fold ? 0 : te) : E;
-    d = ldexp(d, k);
-    dp = ldexp(dp, k);
-}
-
 // Rescale of a scaled chain (every RS_STEPS steps of the convolution walks): once max(|d|, |d_prev|)
 // has reached 1 both are multiplied by exactly 2^-900 and E rises by 900, to a plain double at 0.
 // A chain still scaled afterwards is below 1, so below 2^-900 in truth, which is what RS_STEPS is
@@ -466,94 +374,110 @@ __device__ __forceinline__ double rescale_chain(double& d, double& dp, int& E)
     return f;
 }
 
-// One wave stages a whole block, so that its square roots and divisions keep all lanes busy,
-// and the duty rotates over the workgroup's waves from block to block.
-// Whether this lane's wave stages block `blk` (all of its lanes take part in norm_coefs).
-template <int NT>
-__device__ __forceinline__ bool stage_wave(int tid, int blk)
-{
-    return (tid >> 6) == blk % (NT / 64);
-}
-
 __device__ __forceinline__ size_t packed_index(int lmax, int l, int m)
 {
     return (size_t)m * (size_t)(2 * lmax + 1 - m) / 2 + (size_t)l;
 }
 
 // ================================================================ wigner_d_rings
-template <int R, int NT, int TB>
+// One lane walks one ring of one (mb, msky) pair and stores d^l for every l: NT consecutive rings
+// of a row leave as 512-byte pieces per wave.  A call has few chains (9 pairs on 2001 rings: 284
+// waves on 1024 SIMDs) and up to lmax + 1 steps each, so it is bound by the latency of a step and,
+// with many pairs, by the stores; one chain per lane spreads the walks over the most SIMDs, and NT
+// lanes stage NT values of l at a time.  9 pairs on 2001 rings at lmax 1500: 63 us, 3.4 TB/s of stores
+// (315 us with four chains per lane, coefficients staged by one wave per 32 values of l and a scale
+// check every 8 steps); 100 pairs on 2048 rings at lmax 2048: 595 us, 5.6 TB/s (635 us).  NT 256 took
+// 65 and 620 us, NT 64 64 and 600 us.
+template <int NT>
+struct WignerShared {
+    double2 ab[NT];          // {A', nB'} of the block
+    double ic[NT];           // 1 / c_l
+    NormShared<NT> norm;
+    int grow[NT / RS_STEPS];
+};
+
+template <int NT>
 __global__ void __launch_bounds__(NT) k_wigner(const WignerArgs a)
 {
-    __shared__ double4 cf[2][TB];   // {A', nB', 1/c, -} per l
-    __shared__ double carry[2];
+    __shared__ WignerShared<NT> sh_;
     const int tid = threadIdx.x;
     const int pair = blockIdx.x / a.ntile;
     const int tile = blockIdx.x - pair * a.ntile;
     const int mb = a.col.mb[pair], ms = a.col.ms[pair];
     const int L = a.lmax;
     const int l0 = max(abs(mb), abs(ms));
-    const SeedShape sh = seed_shape(mb, ms);
-    const double lnAh = a.col.lnA[2 * pair], lnAl = a.col.lnA[2 * pair + 1];
-    double* const out = a.d + (size_t)pair * (size_t)(L + 1) * (size_t)a.nring;
-
-    double x[R], d[R], dp[R];
-    int E[R], jj[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int j = tile * (NT * R) + r * NT + tid;
-        jj[r] = j < a.nring ? j : -1;
-        x[r] = 0.0; d[r] = 0.0; dp[r] = 0.0; E[r] = 0;
-        if (jj[r] >= 0) {
-            x[r] = a.ring.x[j];
-            seed_value(lnAh, lnAl, sh, a.ring.lch[j], a.ring.lcl[j], a.ring.lsh[j], a.ring.lsl[j], d[r], E[r]);
-            for (int l = 0; l < l0; ++l) out[(size_t)l * a.nring + j] = 0.0;
-        }
+    const int j = tile * NT + tid;
+    const bool live = j < a.nring;
+    double x = 0.0, d = 0.0, dp = 0.0;
+    int E = 0;
+    double* out = a.d + (size_t)pair * (size_t)(L + 1) * (size_t)a.nring + (live ? j : 0);
+    const size_t row = (size_t)a.nring;
+    if (live) {
+        x = a.ring.x[j];
+        seed_value(a.col.lnA[2 * pair], a.col.lnA[2 * pair + 1], seed_shape(mb, ms), a.ring.lch[j], a.ring.lcl[j],
+                   a.ring.lsh[j], a.ring.lsl[j], d, E);
+#pragma unroll 8
+        for (int l = 0; l < l0; ++l) stg(out + (size_t)l * row, 0.0);
     }
-    bool scaled = false;
-#pragma unroll
-    for (int r = 0; r < R; ++r) scaled |= (E[r] < 0);
-    scaled = wave_any(scaled);
-
-    const int lane = tid & 63;
-    if (stage_wave<NT>(tid, 0)) {
-        const NormCoef k = norm_coefs<TB>(l0, l0, mb, ms, L, true, carry);
-        if (lane < TB) cf[0][lane] = make_double4(k.A, k.nB, k.ic, 0.0);
-    }
-    __syncthreads();
-    const int nblk = (L - l0) / TB + 1;
-    for (int kb = 0; kb < nblk; ++kb) {
-        const int buf = kb & 1;
-        const int lb = l0 + kb * TB;
-        for (int s0 = 0; s0 < TB; s0 += TS) {
-            if (scaled) {
-                bool any = false;
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    check_chain(d[r], dp[r], E[r]);
-                    any |= (E[r] < 0);
-                }
-                scaled = wave_any(any);
-            }
-#pragma unroll
-            for (int t = 0; t < TS; ++t) {
-                const int l = lb + s0 + t;
-                const double4 k = cf[buf][s0 + t];
-#pragma unroll
-                for (int r = 0; r < R; ++r) {
-                    if (jj[r] >= 0 && l <= L)
-                        out[(size_t)l * a.nring + jj[r]] = ((E[r] == 0) ? d[r] : ldexp(d[r], E[r])) * k.z;
-                    const double u = fma(x[r], k.x, k.y);
-                    const double dn = fma(u, d[r], -dp[r]);
-                    dp[r] = d[r];
-                    d[r] = dn;
-                }
-            }
-        }
-        if (stage_wave<NT>(tid, kb + 1) && kb + 1 < nblk) {
-            const NormCoef k = norm_coefs<TB>(lb + TB, l0, mb, ms, L, false, carry);
-            if (lane < TB) cf[buf ^ 1][lane] = make_double4(k.A, k.nB, k.ic, 0.0);
-        }
+    out += (size_t)l0 * row;
+    bool scaled = wave_any(E < 0);
+    NormLane st;
+    auto stage = [&](int lb, bool first) {
+        const NormCoef k = norm_coefs_group<NT>(lb, l0, mb, ms, L, first, st, sh_.norm, sh_.grow);
+        sh_.ab[tid] = make_double2(k.A, k.nB);
+        sh_.ic[tid] = k.ic;
         __syncthreads();
+    };
+    auto step = [&](const double2 k) {
+        const double u = fma(x, k.x, k.y);
+        const double dn = fma(u, d, -dp);
+        dp = d;
+        d = dn;
+    };
+    stage(l0, true);
+    const int n = L - l0 + 1;
+    for (int b0 = 0; b0 < n; b0 += NT) {
+        const int send = min(NT, n - b0);
+        for (int s1 = 0; s1 < send; s1 += RS_STEPS) {
+            if (scaled) {
+                (void)rescale_chain(d, dp, E);
+                scaled = wave_any(E < 0);
+            }
+            const int s2 = min(s1 + RS_STEPS, send);
+            int s = s1;
+            // a group's coefficients are read together and its values stored together: a read and a
+            // branch per step would wait for LDS at every step
+            for (; s + TS <= s2; s += TS) {
+                double2 k[TS];
+                double v[TS];
+#pragma unroll
+                for (int t = 0; t < TS; ++t) { k[t] = sh_.ab[s + t]; v[t] = sh_.ic[s + t]; }
+                if (scaled) {
+#pragma unroll
+                    for (int t = 0; t < TS; ++t) {
+                        v[t] *= ldexp(d, E);
+                        step(k[t]);
+                    }
+                } else {
+#pragma unroll
+                    for (int t = 0; t < TS; ++t) {
+                        v[t] *= d;
+                        step(k[t]);
+                    }
+                }
+                if (live) {
+#pragma unroll
+                    for (int t = 0; t < TS; ++t) stg(out + (size_t)t * row, v[t]);
+                }
+                out += TS * row;
+            }
+            for (; s < s2; ++s) {
+                if (live) stg(out, ldexp(d, E) * sh_.ic[s]);
+                step(sh_.ab[s]);
+                out += row;
+            }
+        }
+        if (b0 + NT < n) stage(l0 + b0 + NT, false);
     }
 }
 
@@ -1577,7 +1501,8 @@ __global__ void __launch_bounds__(256) k_beam_symmetry(const double2* __restrict
 
 // Built tile variants (NT lanes per workgroup).  Forward: R in {2, 4, 8} (polarised: {2, 4}) with
 // NT in {64, 128, 256}; TB shapes no forward kernel (a block is NT values of l).  Adjoint: R in
-// {2, 4, 8}, TB 32 with each NT, TB 64 with NT 256.  Wigner: R in {1, 4}, NT 256, TB 32.
+// {2, 4, 8}, TB 32 with each NT, TB 64 with NT 256.  Wigner: NT 128 with one chain per lane (R in {1, 4} is
+// accepted and shapes nothing).
 bool tile_supported(int op, Tile t)
 {
     const bool nt_ok = t.NT == 64 || t.NT == 128 || t.NT == 256;
@@ -1592,12 +1517,8 @@ bool tile_supported(int op, Tile t)
 
 int launch_wigner(const WignerArgs& a, Tile t, void* stream)
 {
-    const int blocks = a.npair * a.ntile;
-    switch (t.R) {
-    case 1: return launch_grid(k_wigner<1, 256, 32>, a, blocks, 256, stream);
-    case 4: return launch_grid(k_wigner<4, 256, 32>, a, blocks, 256, stream);
-    default: return (int)hipErrorInvalidValue;
-    }
+    if (t.R != 1 || t.NT != 128) return (int)hipErrorInvalidValue;   // a.ntile counts tiles of 128 rings
+    return launch_grid(k_wigner<128>, a, a.npair * a.ntile, 128, stream);
 }
 
 // Maps a runtime (R, NT[, TB]) onto the template instantiation F<R, NT[, TB]>.

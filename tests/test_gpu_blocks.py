@@ -78,3 +78,21 @@ def test_ring_slots_around_workgroups(B, nslot, beam):
     assert np.linalg.norm(ga.cpu().numpy() - ga_ref) <= TOL * np.linalg.norm(ga_ref)
     for r in range(2 * M + 1):
         assert np.linalg.norm(gb.cpu().numpy()[r] - gb_ref[r]) <= TOL * np.linalg.norm(gb_ref[r])
+
+
+@pytest.mark.parametrize("L, nring", [(0, 1), (7, 127), (8, 128), (127, 129), (128, 5), (300, 257), (700, 40)])
+def test_wigner_rows_around_blocks(B, L, nring):
+    """d^l for chosen pairs at the edges of staged blocks (128 values of l) and workgroups (128 rings),
+    from both poles to the equator: rows that start below the double range among them.  Gate: the
+    repository's absolute 1e-10; where the oracle is an exact zero, or below the double range, so is d."""
+    import oracle
+    x = np.cos(np.linspace(0.0, np.pi, nring)) if nring > 1 else np.array([0.3])
+    mb = np.array([0, 2, -3, 5, -L, L, 1], np.int32).clip(-L, L)
+    ms = np.array([0, L, L // 2, -(L // 3), L, -L, 1], np.int32).clip(-L, L)
+    print(f"[gpu] wigner L={L} nring={nring}", flush=True)
+    d = B.wigner_d_rings_x(L, mb, ms, x).cpu().numpy()
+    ref = oracle.wigner_d(L, mb, ms, x)
+    assert np.abs(d - ref).max() <= 1e-10
+    assert np.all(np.abs(d[np.abs(ref) < 1e-307]) < 1e-306)
+    big = np.abs(ref) > 1e-250
+    assert np.abs(d[big] / ref[big] - 1).max() <= 1e-6    # small values keep their relative accuracy
