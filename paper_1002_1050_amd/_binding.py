@@ -177,6 +177,16 @@ def _fn(name, cos):
     return getattr(lib(), name + ("_x" if cos else ""))
 
 
+def _ring_cosines(rings, cos):
+    """(rings, cos) for the twin of an entry point on ring cosines, the cosines formed once for the
+    workspace query and the call; colatitudes that are refused stay, for the entry point to report."""
+    r = _host(rings, np.float64)
+    if cos:
+        return r, True
+    x = np.empty_like(r)
+    return (r, False) if lib().tc_rings_from_beta(r.size, _hptr(r), _hptr(x)) else (x, True)
+
+
 def _workspace_bytes(op, lmax, mbmax, rings, cos):
     return int(_fn("totalconv_workspace_bytes_rings", cos)(op, lmax, mbmax, rings.size, _hptr(rings)))
 
@@ -264,7 +274,7 @@ def _sky_beam(torch, lmax, mbmax, alm, blm, device=None, tag=""):
 def _totalconv_fwd(lmax, mbmax, rings, cos, alm, blm, out):
     import torch
     device = _sky_beam(torch, lmax, mbmax, alm, blm)
-    x = _host(rings, np.float64)
+    x, on_x = _ring_cosines(rings, cos)
     shape = (2 * mbmax + 1, lmax + 1, x.size)
     if out is None:
         out = torch.empty(shape, dtype=torch.complex128, device=device)
@@ -273,8 +283,8 @@ def _totalconv_fwd(lmax, mbmax, rings, cos, alm, blm, out):
         if tuple(out.shape) != shape or out.device != device:
             raise ValueError(f"out must have shape {shape} on {device}")
     stream = _stream_handle(torch, device)
-    ws = workspace_cache.get(torch, device, stream, _workspace_bytes(TC_OP_FWD, lmax, mbmax, x, cos))
-    rc = _fn("totalconv_fwd", cos)(lmax, mbmax, x.size, _hptr(x), _dptr(alm), _dptr(blm), _dptr(out),
+    ws = workspace_cache.get(torch, device, stream, _workspace_bytes(TC_OP_FWD, lmax, mbmax, x, on_x))
+    rc = _fn("totalconv_fwd", on_x)(lmax, mbmax, x.size, _hptr(x), _dptr(alm), _dptr(blm), _dptr(out),
                                    _dptr(ws), ws.numel(), stream)
     _check("totalconv_fwd" + ("_x" if cos else ""), rc)
     return out
@@ -310,7 +320,7 @@ def _totalconv_adj(lmax, mbmax, rings, cos, alm, blm, Cbar, want_alm, want_blm):
     import torch
     device = _sky_beam(torch, lmax, mbmax, alm, blm)
     _require_device(Cbar, "Cbar", torch.complex128)
-    x = _host(rings, np.float64)
+    x, on_x = _ring_cosines(rings, cos)
     if Cbar.numel() != (2 * mbmax + 1) * (lmax + 1) * x.size or Cbar.device != device:
         raise ValueError("Cbar must hold (2*mbmax+1, lmax+1, nring) values on the device of alm")
     if not want_alm and not want_blm:
@@ -318,8 +328,8 @@ def _totalconv_adj(lmax, mbmax, rings, cos, alm, blm, Cbar, want_alm, want_blm):
     alm_bar = torch.empty_like(alm) if want_alm else None
     blm_bar = torch.empty_like(blm) if want_blm else None
     stream = _stream_handle(torch, device)
-    ws = workspace_cache.get(torch, device, stream, _workspace_bytes(TC_OP_ADJ, lmax, mbmax, x, cos))
-    rc = _fn("totalconv_adj", cos)(lmax, mbmax, x.size, _hptr(x), _dptr(alm), _dptr(blm), _dptr(Cbar),
+    ws = workspace_cache.get(torch, device, stream, _workspace_bytes(TC_OP_ADJ, lmax, mbmax, x, on_x))
+    rc = _fn("totalconv_adj", on_x)(lmax, mbmax, x.size, _hptr(x), _dptr(alm), _dptr(blm), _dptr(Cbar),
                                    _dptr(alm_bar), _dptr(blm_bar), _dptr(ws), ws.numel(), stream)
     _check("totalconv_adj" + ("_x" if cos else ""), rc)
     return alm_bar, blm_bar
@@ -356,13 +366,13 @@ def _totalconv_fwd_pol(lmax, mbmax, rings, cos, alms, blms, mode):
     import torch
     alms, blms = _pol_inputs(torch, lmax, mbmax, alms, blms)
     device = alms[0].device
-    x = _host(rings, np.float64)
+    x, on_x = _ring_cosines(rings, cos)
     nout = 1 if mode == TC_POL_SUM else len(alms)
     outs = [torch.empty((2 * mbmax + 1, lmax + 1, x.size), dtype=torch.complex128, device=device)
             for _ in range(nout)]
     stream = _stream_handle(torch, device)
-    ws = workspace_cache.get(torch, device, stream, _workspace_bytes(TC_OP_FWD_POL, lmax, mbmax, x, cos))
-    rc = _fn("totalconv_fwd_pol", cos)(lmax, mbmax, x.size, _hptr(x), len(alms), _ptr_array(alms),
+    ws = workspace_cache.get(torch, device, stream, _workspace_bytes(TC_OP_FWD_POL, lmax, mbmax, x, on_x))
+    rc = _fn("totalconv_fwd_pol", on_x)(lmax, mbmax, x.size, _hptr(x), len(alms), _ptr_array(alms),
                                        _ptr_array(blms), mode, _ptr_array(outs), _dptr(ws), ws.numel(), stream)
     _check("totalconv_fwd_pol" + ("_x" if cos else ""), rc)
     return outs
@@ -383,7 +393,7 @@ def _totalconv_adj_pol(lmax, mbmax, rings, cos, alms, blms, Cbars, mode, want_al
     import torch
     alms, blms = _pol_inputs(torch, lmax, mbmax, alms, blms)
     Cbars = list(Cbars)
-    x = _host(rings, np.float64)
+    x, on_x = _ring_cosines(rings, cos)
     if len(Cbars) != (1 if mode == TC_POL_SUM else len(alms)):
         raise ValueError("one cotangent per output is required")
     device = alms[0].device
@@ -394,8 +404,8 @@ def _totalconv_adj_pol(lmax, mbmax, rings, cos, alms, blms, Cbars, mode, want_al
     abar = [torch.empty_like(a) if want_alm else None for a in alms]
     bbar = [torch.empty_like(b) if want_blm else None for b in blms]
     stream = _stream_handle(torch, device)
-    ws = workspace_cache.get(torch, device, stream, _workspace_bytes(TC_OP_ADJ, lmax, mbmax, x, cos))
-    rc = _fn("totalconv_adj_pol", cos)(lmax, mbmax, x.size, _hptr(x), len(alms), _ptr_array(alms),
+    ws = workspace_cache.get(torch, device, stream, _workspace_bytes(TC_OP_ADJ, lmax, mbmax, x, on_x))
+    rc = _fn("totalconv_adj_pol", on_x)(lmax, mbmax, x.size, _hptr(x), len(alms), _ptr_array(alms),
                                        _ptr_array(blms), mode, _ptr_array(Cbars),
                                        _ptr_array(abar) if want_alm else None,
                                        _ptr_array(bbar) if want_blm else None, _dptr(ws), ws.numel(), stream)

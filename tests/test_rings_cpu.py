@@ -75,3 +75,22 @@ def test_library_rings_equal_the_oracle(orc, name):
     got = B.rings_from_beta(beta)
     ref = orc.ring_grid_x(beta)
     assert got.tobytes() == ref.tobytes()
+
+
+@pytest.mark.parametrize("name", ["random", "equator", "table points", "poles", "midpoints", "descending pairs"])
+def test_ring_cosines_equal_long_double_rounded_once(orc, name):
+    """The library's own cosine against the oracle's, where its rounding is hardest to be sure of: many
+    random colatitudes, the equator (tiny cosines), its table's points k/32 and their midpoints, the poles."""
+    from paper_1002_1050_amd import _binding as B
+    rng = np.random.Generator(np.random.PCG64(32))
+    k = np.arange(101)
+    beta = {
+        "random": rng.uniform(0.0, np.pi, 200001),
+        "equator": np.pi / 2 + np.concatenate([np.linspace(-1e-3, 1e-3, 20001), 2.0 ** -np.arange(1, 60), [0.0]]),
+        "table points": np.concatenate([k / 32.0, np.nextafter(k[1:] / 32.0, 0.0), np.nextafter(k[:100] / 32.0, 4.0)]),
+        "poles": np.concatenate([np.linspace(0.0, 1e-3, 5001), 2.0 ** -np.arange(1.0, 1070.0, 7.0),
+                                 np.pi - np.linspace(0.0, 1e-6, 5001), [np.nextafter(np.pi, 0.0)]]),
+        "midpoints": (k[:100] + 0.5) / 32.0,
+        "descending pairs": S.ring_colatitudes(3001)[::-1].copy(),
+    }[name]
+    assert B.rings_from_beta(beta).tobytes() == orc.ring_grid_x(beta).tobytes()
