@@ -557,6 +557,8 @@ int fwd_impl(int op, int lmax, int mbmax, int nring, const double* cosbeta, int 
         int* sym = reinterpret_cast<int*>(static_cast<char*>(workspace) + L.sym);
         if ((rc = tc::launch_beam_symmetry(blm[0], lmax, mbmax, sym, stream))) return hip_fail(rc, "beam symmetry launch");
         a.beam_sym[0] = sym;
+    } else if (!sum) {     // polarised pairs: the launch finds their rows' signs and keeps them here
+        a.beam_sym[0] = reinterpret_cast<const int*>(static_cast<char*>(workspace) + L.sym);
     }
     rc = timed_launch(op, stream, [&] { return tc::launch_fwd(a, t, stream); });
     return rc ? hip_fail(rc, "totalconv_fwd launch") : TC_OK;

@@ -60,7 +60,8 @@ struct FwdArgs {
     double* C[kMaxPairs];          // [2 pmbmax+1][L+1][nring] complex, per output
     const int* beam_sym[kMaxPairs];  // scalar convolution: per beam row mb + pmbmax, s = +-1 if
                            // b_{l,-mb} = s b_{l,mb} for every l >= |mb|, else 0 (from k_beam_symmetry);
-                           // null: not used (polarised)
+                           // null: not used.  Polarised with separate outputs: [0] is scratch of
+                           // 2 mbmax + 1 ints for the pairs' signs, filled by launch_fwd; summed: null
 };
 
 struct AdjArgs {
