@@ -406,7 +406,7 @@ int upload(void* ws, const std::vector<char>& img, void* stream)
 
 // Host images of the per-call tables, kept in pinned memory for repeated calls with the same
 // (kind, sizes, tile, ring set, pair list) on the same device: a repeated call skips the long
-// double prep and the column sort, and its upload is an asynchronous copy from pinned memory.
+// double prep and the column sort, and its upload is a kernel that reads the mapped image (launch_prep).
 // Least recently used entries are dropped beyond kCacheEntries or kCacheBytes, after their last
 // upload has completed.  The images never change once built.
 struct TableImage {
@@ -414,6 +414,7 @@ struct TableImage {
     std::vector<double> x;          // ring cosines
     std::vector<int> pairs;         // (mb, msky) pairs of wigner_d_rings
     void* pinned = nullptr;
+    void* mapped = nullptr;         // `pinned` as the device sees it
     size_t bytes = 0;
     hipEvent_t done = nullptr;      // recorded after the last upload from `pinned`
 };
@@ -442,11 +443,22 @@ bool same_key(const TableImage& e, const std::vector<int>& head, int nring, cons
     return true;
 }
 
+// The row signs of a call's beams (npair 0: none wanted).
+int launch_signs(tc::PrepArgs signs, void* stream)
+{
+    if (signs.npair == 0) return TC_OK;
+    signs.bytes = 0;
+    const int rc = tc::launch_prep ? tc::launch_prep(signs, stream) : (int)hipErrorInvalidDeviceFunction;
+    return rc ? hip_fail(rc, "beam symmetry launch") : TC_OK;
+}
+
 // Upload the table image for this call into the workspace, building it on a miss with
-// build(img).  kind: TC_OP_* of the layout.  For wigner_d_rings pass the pairs (else npair 0).
+// build(img), and find the row signs of its beams.  kind: TC_OP_* of the layout.  For wigner_d_rings
+// pass the pairs (else npair 0).
 template <class Build>
 int upload_tables(int kind, int lmax, int mbmax_or_npair, int nring, const double* x, int npair, const int* mb,
-                  const int* ms, const Layout& L, tc::Tile t, void* ws, void* stream, Build build)
+                  const int* ms, const Layout& L, tc::Tile t, void* ws, void* stream, Build build,
+                  tc::PrepArgs signs = tc::PrepArgs{})
 {
     int dev = 0;
     int rc = (int)hipGetDevice(&dev);
@@ -469,7 +481,12 @@ int upload_tables(int kind, int lmax, int mbmax_or_npair, int nring, const doubl
         if (rc) {   // no pinned memory: upload from the pageable image, uncached
             (void)hipGetLastError();
             release_image(e);
-            return upload(ws, img, stream);
+            rc = upload(ws, img, stream);
+            return rc ? rc : launch_signs(signs, stream);
+        }
+        if (hipHostGetDevicePointer(&e.mapped, e.pinned, 0) != hipSuccess) {
+            (void)hipGetLastError();
+            e.mapped = nullptr;
         }
         std::memcpy(e.pinned, img.data(), e.bytes);
         g_cache.push_front(std::move(e));
@@ -485,9 +502,15 @@ int upload_tables(int kind, int lmax, int mbmax_or_npair, int nring, const doubl
         g_cache.splice(g_cache.begin(), g_cache, it);
         it = g_cache.begin();
     }
-    rc = (int)hipMemcpyAsync(ws, it->pinned, it->bytes, hipMemcpyHostToDevice, (hipStream_t)stream);
+    if (tc::launch_prep && it->mapped) {
+        signs.src = it->mapped; signs.dst = ws; signs.bytes = it->bytes;
+        rc = tc::launch_prep(signs, stream);
+        signs.npair = 0;
+    } else {
+        rc = (int)hipMemcpyAsync(ws, it->pinned, it->bytes, hipMemcpyHostToDevice, (hipStream_t)stream);
+    }
     if (!rc) rc = (int)hipEventRecord(it->done, (hipStream_t)stream);
-    return rc ? hip_fail(rc, "table upload (hipMemcpyAsync)") : TC_OK;
+    return rc ? hip_fail(rc, "table upload") : launch_signs(signs, stream);
 }
 
 tc::RingTables ring_ptrs(void* ws, const Layout& L, int nring)
@@ -534,12 +557,20 @@ int fwd_impl(int op, int lmax, int mbmax, int nring, const double* cosbeta, int 
         build_slots(nring, cosbeta, img, L);
         build_columns(lmax, mbmax, img, L);
     };
+    // columns whose beam rows are related by a sign take the even / odd sums (summed pairs have no use for it)
+    tc::PrepArgs signs{};
+    if (npair == 1 || !sum) {
+        signs.npair = npair; signs.lmax = lmax; signs.mbmax = mbmax;
+        for (int p = 0; p < npair; ++p) signs.blm[p] = blm[p];
+        signs.sym = reinterpret_cast<int*>(static_cast<char*>(workspace) + L.sym);
+    }
     if (cached) {
-        rc = upload_tables(TC_OP_FWD, lmax, mbmax, nring, cosbeta, 0, nullptr, nullptr, L, t, workspace, stream, build);
+        rc = upload_tables(TC_OP_FWD, lmax, mbmax, nring, cosbeta, 0, nullptr, nullptr, L, t, workspace, stream, build,
+                           signs);
     } else {   // no pinned image: built here and copied from pageable host memory
         std::vector<char> img(L.tables_end, 0);
         build(img);
-        rc = upload(workspace, img, stream);
+        if (!(rc = upload(workspace, img, stream))) rc = launch_signs(signs, stream);
     }
     if (rc) return rc;
     tc::FwdArgs a{};
@@ -553,13 +584,7 @@ int fwd_impl(int op, int lmax, int mbmax, int nring, const double* cosbeta, int 
     a.sum = sum;
     for (int p = 0; p < npair; ++p) { a.alm[p] = alm[p]; a.blm[p] = blm[p]; a.pmbmax[p] = mbmax; }
     for (int c = 0; c < nout; ++c) a.C[c] = C[c];
-    if (npair == 1) {   // scalar convolution: beam rows related by a sign take the even / odd sums
-        int* sym = reinterpret_cast<int*>(static_cast<char*>(workspace) + L.sym);
-        if ((rc = tc::launch_beam_symmetry(blm[0], lmax, mbmax, sym, stream))) return hip_fail(rc, "beam symmetry launch");
-        a.beam_sym[0] = sym;
-    } else if (!sum) {     // polarised pairs: the launch finds their rows' signs and keeps them here
-        a.beam_sym[0] = reinterpret_cast<const int*>(static_cast<char*>(workspace) + L.sym);
-    }
+    a.beam_sym[0] = signs.sym;
     rc = timed_launch(op, stream, [&] { return tc::launch_fwd(a, t, stream); });
     return rc ? hip_fail(rc, "totalconv_fwd launch") : TC_OK;
 }
@@ -590,12 +615,24 @@ int adj_impl(int lmax, int mbmax, int nring, const double* cosbeta, int npair, c
     const tc::Tile t = call_tile(TC_OP_ADJ, lmax, count_slots(nring, cosbeta));
     const Layout L = make_layout(TC_OP_ADJ, lmax, mbmax, nring, cosbeta, t);
     if ((rc = check_ws(L, workspace, ws_bytes)) || (rc = check_grid(L))) return rc;
+    // The sky gradient of one pair alone: with the row signs of its beam, a column whose rows are
+    // related by one forms one sum instead of two.  The signs (2 mbmax + 1 ints) lie in front of V:
+    // the first mbmax complex values of its row mb = -mbmax are those of l < mbmax at msky = 0, which
+    // no column writes and no epilogue reads.
+    int* const sym = reinterpret_cast<int*>(static_cast<char*>(workspace) + L.V);
+    auto sky_alone = [&](int p0, int p1) {
+        return p1 - p0 == 1 && mbmax >= 1 && alm_bar && alm_bar[p0] && !(blm_bar && blm_bar[p0]);
+    };
+    tc::PrepArgs signs{};
+    if (sky_alone(0, npair)) {
+        signs.npair = 1; signs.lmax = lmax; signs.mbmax = mbmax; signs.blm[0] = blm[0]; signs.sym = sym;
+    }
     rc = upload_tables(TC_OP_FWD, lmax, mbmax, nring, cosbeta, 0, nullptr, nullptr, L, t, workspace, stream,
                        [&](std::vector<char>& img) {
                            build_rings(nring, cosbeta, img, L);
                            build_slots(nring, cosbeta, img, L);
                            build_columns(lmax, mbmax, img, L);
-                       });
+                       }, signs);
     if (rc) return rc;
     tc::AdjArgs a{};
     a.lmax = lmax; a.mbmax = mbmax; a.nring = nring; a.nslot = L.nslot; a.ncol = L.ncol; a.ntile = L.ntile;
@@ -615,14 +652,9 @@ int adj_impl(int lmax, int mbmax, int nring, const double* cosbeta, int npair, c
             need |= (alm_bar && alm_bar[p]) || (blm_bar && blm_bar[p]);
         if (!need) continue;
         a.Cbar[0] = Cbar[k];
-        // The sky gradient of one pair alone: with the row signs of its beam, a column whose rows are
-        // related by one forms one sum instead of two.  The signs (2 mbmax + 1 ints) lie in front of V:
-        // the first mbmax complex values of its row mb = -mbmax are those of l < mbmax at msky = 0, which
-        // no column writes and no epilogue reads.
         a.beam_sym = nullptr;
-        if (p1 - p0 == 1 && mbmax >= 1 && !(blm_bar && blm_bar[p0])) {
-            int* sym = reinterpret_cast<int*>(a.V[0]);
-            if ((rc = tc::launch_beam_symmetry(blm[p0], lmax, mbmax, sym, stream)))
+        if (sky_alone(p0, p1)) {
+            if (npair > 1 && (rc = tc::launch_beam_symmetry(blm[p0], lmax, mbmax, sym, stream)))   // V is reused
                 return hip_fail(rc, "beam symmetry launch");
             a.beam_sym = sym;
         }

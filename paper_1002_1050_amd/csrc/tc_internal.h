@@ -60,8 +60,8 @@ struct FwdArgs {
     double* C[kMaxPairs];          // [2 pmbmax+1][L+1][nring] complex, per output
     const int* beam_sym[kMaxPairs];  // scalar convolution: per beam row mb + pmbmax, s = +-1 if
                            // b_{l,-mb} = s b_{l,mb} for every l >= |mb|, else 0 (from k_beam_symmetry);
-                           // null: not used.  Polarised with separate outputs: [0] is scratch of
-                           // 2 mbmax + 1 ints for the pairs' signs, filled by launch_fwd; summed: null
+                           // null: not used.  Polarised with separate outputs: [0] holds per row a word
+                           // with pair p's sign + 1 in byte p (from launch_prep); summed: null
 };
 
 struct AdjArgs {
@@ -141,6 +141,18 @@ int launch_wigner(const WignerArgs& a, Tile t, void* stream);
 int launch_fwd(const FwdArgs& a, Tile t, void* stream);
 int launch_beam_symmetry(const double* blm, int lmax, int mbmax, int* sym, void* stream);
 int launch_adj(const AdjArgs& a, Tile t, void* stream);
+// What a call needs before its walks: `bytes` of tables from mapped host memory (both sides 16-byte
+// aligned, bytes a multiple of 16; 0: none) and, with npair > 0, the row signs of npair beams.
+struct PrepArgs {
+    const void* src;
+    void* dst;
+    size_t bytes;
+    int npair, lmax, mbmax;
+    const double* blm[3];
+    int* sym;              // [2 mbmax + 1]: the sign (npair 1) or the word of FwdArgs::beam_sym
+};
+// Weak: a program of the host side alone (no kernels) has none, and copies with the runtime.
+int launch_prep(const PrepArgs& a, void* stream) __attribute__((weak));
 int launch_adj_epilogue(const EpiArgs& e, void* stream);
 // tc_epilogue.hip: the sky gradients of every pair in one launch, U and V read once.
 int launch_adj_sky_pairs(const EpiPairsArgs& e, void* stream);

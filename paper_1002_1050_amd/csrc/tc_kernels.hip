@@ -847,7 +847,7 @@ __device__ __forceinline__ int row_sign(const FwdArgs& a, int p, int mb)
     return related_sign(a.beam_sym[p], a.pmbmax[p], mb);
 }
 
-// The signs of the NC polarised pairs for row mb, from the words that k_pol_symmetry packs (pair p's
+// The signs of the NC polarised pairs for row mb, from the words that k_prep packs (pair p's
 // sign + 1 in byte p); whether the column takes the even / odd form: all rows related, and not row 0
 // alone (as related_sign).
 template <int NC>
@@ -1523,52 +1523,68 @@ int launch_grid(void (*kern)(Args), const Args& a, int blocks, int nt, void* str
     return (int)hipGetLastError();
 }
 
-// Beam rows related by a sign: sym[M + mb] = sym[M - mb] = s if b_{l,-mb} = s b_{l,mb} for
-// every l >= |mb| (s = +1 when both signs hold, as for zero rows and mb = 0), else 0.
-__global__ void __launch_bounds__(256) k_beam_symmetry(const double2* __restrict__ blm, int lmax, int mbmax,
-                                                       int* __restrict__ sym)
+// Whether row mb of a beam equals row -mb up to a sign for every l >= mb: +1 (also when both signs hold, as
+// for zero rows and mb = 0), -1, or 0.  All threads of the workgroup take part.
+__device__ __forceinline__ int beam_row_sign(const double2* blm, int lmax, int mbmax, int mb)
 {
-    const int mb = blockIdx.x;   // 0 .. mbmax
     const double2* bp = blm + (size_t)(mbmax + mb) * (lmax + 1);
     const double2* bm = blm + (size_t)(mbmax - mb) * (lmax + 1);
     bool plus = true, minus = true;
     for (int l = mb + (int)threadIdx.x; l <= lmax; l += 256) {
-        const double2 p = bp[l], m = bm[l];
+        const double2 p = ldg(bp + l), m = ldg(bm + l);
         plus = plus && (m.x == p.x) && (m.y == p.y);
         minus = minus && (m.x == -p.x) && (m.y == -p.y);
     }
     plus = __syncthreads_and(plus);
     minus = __syncthreads_and(minus);
+    return plus ? 1 : (minus ? -1 : 0);
+}
+
+// Row signs of one beam: sym[M + mb] = sym[M - mb], one workgroup per mb = 0 .. mbmax.
+__global__ void __launch_bounds__(256) k_beam_symmetry(const double2* __restrict__ blm, int lmax, int mbmax,
+                                                       int* __restrict__ sym)
+{
+    const int mb = blockIdx.x;
+    const int s = beam_row_sign(blm, lmax, mbmax, mb);
     if (threadIdx.x == 0) {
-        const int s = plus ? 1 : (minus ? -1 : 0);
         sym[mbmax + mb] = s;
         sym[mbmax - mb] = s;
     }
 }
 
-// The same for up to three pairs: sym[M + mb] = sym[M - mb] holds pair p's sign + 1 in byte p.
-struct PolBeams { const double2* blm[3]; };
-__global__ void __launch_bounds__(256) k_pol_symmetry(const PolBeams b, int npair, int lmax, int mbmax,
-                                                      int* __restrict__ sym)
+// What a call needs before its walks, in one launch: its tables, read by the copy workgroups from the
+// pinned host image (mapped memory) into the workspace, and the row signs of its beams by mbmax + 1 more
+// (for two or three polarised pairs, pair p's sign + 1 in byte p of a word).  A copy by the DMA engine and
+// the kernel that waits for it cost 20 to 27 us of a small call; this launch takes 4 to 5.
+constexpr int PREP_LOADS = 4;   // 16-byte loads in flight per lane
+__global__ void __launch_bounds__(256) k_prep(const PrepArgs a, int ncopy)
 {
-    const int mb = blockIdx.x;   // 0 .. mbmax
-    int word = 0;
-    for (int p = 0; p < npair; ++p) {
-        const double2* bp = b.blm[p] + (size_t)(mbmax + mb) * (lmax + 1);
-        const double2* bm = b.blm[p] + (size_t)(mbmax - mb) * (lmax + 1);
-        bool plus = true, minus = true;
-        for (int l = mb + (int)threadIdx.x; l <= lmax; l += 256) {
-            const double2 v = bp[l], m = bm[l];
-            plus = plus && (m.x == v.x) && (m.y == v.y);
-            minus = minus && (m.x == -v.x) && (m.y == -v.y);
-        }
-        plus = __syncthreads_and(plus);
-        minus = __syncthreads_and(minus);
-        word |= (plus ? 2 : minus ? 0 : 1) << (8 * p);
+    const int tid = threadIdx.x;
+    if ((int)blockIdx.x < ncopy) {
+        typedef unsigned v4 __attribute__((ext_vector_type(4)));
+        const v4* src = static_cast<const v4*>(a.src);
+        v4* dst = static_cast<v4*>(a.dst);
+        const size_t n = a.bytes / 16, i0 = (size_t)blockIdx.x * (256 * PREP_LOADS) + tid;
+        v4 v[PREP_LOADS];
+#pragma unroll
+        for (int k = 0; k < PREP_LOADS; ++k)
+            if (i0 + 256 * k < n) v[k] = src[i0 + 256 * k];
+#pragma unroll
+        for (int k = 0; k < PREP_LOADS; ++k)
+            if (i0 + 256 * k < n) dst[i0 + 256 * k] = v[k];
+        return;
     }
-    if (threadIdx.x == 0) {
-        sym[mbmax + mb] = word;
-        sym[mbmax - mb] = word;
+    const int mb = blockIdx.x - ncopy;
+    int word = 0;
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+        if (p < a.npair) {
+            const int s = beam_row_sign(reinterpret_cast<const double2*>(a.blm[p]), a.lmax, a.mbmax, mb);
+            word |= a.npair == 1 ? s : (s + 1) << (8 * p);
+        }
+    if (tid == 0) {
+        a.sym[a.mbmax + mb] = word;
+        a.sym[a.mbmax - mb] = word;
     }
 }
 
@@ -1615,6 +1631,15 @@ int launch_beam_symmetry(const double* blm, int lmax, int mbmax, int* sym, void*
     return (int)hipGetLastError();
 }
 
+int launch_prep(const PrepArgs& a, void* stream)
+{
+    const int ncopy = (int)((a.bytes / 16 + 256 * PREP_LOADS - 1) / (256 * PREP_LOADS));
+    const int blocks = ncopy + (a.npair > 0 ? a.mbmax + 1 : 0);
+    if (blocks == 0) return 0;
+    hipLaunchKernelGGL(k_prep, dim3(blocks), dim3(256), 0, (hipStream_t)stream, a, ncopy);
+    return (int)hipGetLastError();
+}
+
 int launch_fwd(const FwdArgs& a, Tile t, void* stream)
 {
     const int blocks = a.ncol * a.ntile;
@@ -1634,12 +1659,8 @@ int launch_fwd(const FwdArgs& a, Tile t, void* stream)
         return (int)hipErrorInvalidValue;
     }
     const int nc = a.sum ? 1 : a.npair;
-    if (nc > 1 && a.beam_sym[0]) {   // the pairs' row signs, then the columns where all are related
-        PolBeams b{};
-        for (int p = 0; p < a.npair; ++p) b.blm[p] = reinterpret_cast<const double2*>(a.blm[p]);
-        hipLaunchKernelGGL(k_pol_symmetry, dim3(a.mbmax + 1), dim3(256), 0, (hipStream_t)stream, b, a.npair, a.lmax,
-                           a.mbmax, const_cast<int*>(a.beam_sym[0]));
-        int rc = (int)hipGetLastError();
+    if (nc > 1 && a.beam_sym[0]) {   // the columns where every pair's rows are related
+        int rc = 0;
 #define Y(r, nt, c) if (!rc && t.R == r && t.NT == nt && nc == c) rc = launch_grid(k_fwd_pol_rows<r, nt, c>, a, blocks, nt, stream);
         TC_POL_ROWS_VARIANTS(Y)
 #undef Y
