@@ -141,7 +141,6 @@ int wigner_d_rings_x(int lmax, int npair, const int* mb, const int* msky,
  *   d            out: [nring][2l+1][2l+1] doubles, d[j][m+l][m'+l] = d^l_{m m'}(beta_j);
  *                values below the double range come out as 0 or subnormal
  *   workspace    at least wigner_d_matrix_workspace_bytes(l, nring) bytes
- * tc_set_tile(TC_OP_MATRIX, R) picks R in {1, 2} rows per lane (0: built-in).
  */
 size_t wigner_d_matrix_workspace_bytes(int l, int nring);
 int wigner_d_matrix(int l, int nring, const double* beta, double* d,
@@ -291,9 +290,8 @@ int totalconv_datacube(int lmax, int mbmax, int nring, const double* C, int nalp
  * Tile selection for later calls in this process (not in the paper; a tuning
  * knob of this implementation).  Each lane walks R chains; a workgroup covers
  * 256*R ring slots of one column.  op = TC_OP_FWD or TC_OP_ADJ (R in {2, 4, 8}),
- * TC_OP_FWD_POL (R in {2, 4}), TC_OP_WIGNER (R in {1, 4}, without effect) or TC_OP_MATRIX (R in
- * {1, 2}: one-wave workgroups with R rows per lane in place of the built-in two-wave
- * workgroups with one row per lane); for TC_OP_CUBE, R > 0 sets the rings the data cube processes per chunk
+ * TC_OP_FWD_POL (R in {2, 4}), TC_OP_WIGNER (R in {1, 4}) or TC_OP_MATRIX (R in {1, 2}), the last
+ * two accepted without effect (one shape is built); for TC_OP_CUBE, R > 0 sets the rings the data cube processes per chunk
  * (and so its workspace).  R = 0 restores the built-in choice.  Affects
  * the workspace sizes reported afterwards.  Returns TC_EINVAL for other values.
  * Not synchronised: set it from the thread that issues the calls.
