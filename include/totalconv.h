@@ -273,10 +273,10 @@ int totalconv_adj_pol_x(int lmax, int mbmax, int nring, const double* cosbeta, i
  *                evaluated on that grid requires)
  *   cube         out: [nring][nalpha][ngamma] doubles, 16-byte aligned
  *   workspace    at least totalconv_datacube_workspace_bytes(...) bytes: the
- *                phase and twiddle tables and the alpha sums of two ring chunks
- *                (rings are processed in chunks of about 768 MB of alpha sums, the
- *                sums over mb of one chunk formed while the FFTs of the chunk
- *                before run on a second stream of the library)
+ *                phase and twiddle tables and the alpha sums of one ring chunk
+ *                (rings are processed in equal chunks of at most 2 GB of alpha sums,
+ *                all on `stream`); the size of earlier versions, two chunks of
+ *                768 MB, is still enough
  * TC_EUNSUPPORTED if the device allows less LDS per workgroup than the FFT of
  * length ngamma needs (8.5 * ngamma + 16 bytes).
  * totalconv_datacube_ring_chunk returns the rings per chunk (0 for bad sizes).

@@ -7,8 +7,10 @@
 // taken from C_{-mb,-msky} = conj(C_{mb,msky}) (real sky and beam, Sec. 4.2.3), so
 // that c is real.
 //
-// Two passes, both bound by HBM bandwidth (the host runs them over ring chunks, the alpha pass of
-// one chunk beside the gamma pass of the chunk before):
+// Two passes over each chunk of rings, both bound by HBM bandwidth.  At lmax 2048, mbmax 14, 2000 rings,
+// 29 x 4096 angles (1.9 GB of C in, 1.9 GB of P out and in, 1.9 GB of cube out) they take 0.98 and 0.84 ms,
+// 3.9 and 4.5 TB/s of reads and writes together (2.53 ms before the rows of P were padded to whole lines, the
+// passes taken one after the other and the gamma pass given workgroups of the row's size; 1.90 ms the call now):
 //  1. k_cube_alpha: P[j][a][k] = sum_mb E[mb][a] C[mb][k][j] for k = msky >= 0 -- the
 //     short sum over mb, done directly with the host's phase table E (read into scalar
 //     registers, four phases per load), and the
@@ -46,7 +48,10 @@ __device__ __forceinline__ void store_stream(double2* p, double2 v)
 }
 
 // ------------------------------------------------------------ alpha sums
-constexpr int CA_T = 16;    // rings and msky values per workgroup tile (16 x 16 = 256 lanes)
+// A workgroup's tile: CA_J rings (256-byte reads of C) by CA_K values of msky (256-byte stores of P, whole
+// lines: the rows of P are padded to lines).  Tiles of 16 x 32 or 32 x 16 with 512 lanes took 3 to 6% longer
+// (two workgroups' barriers per compute unit instead of four).
+constexpr int CA_J = 16, CA_K = 16, CA_NT = CA_J * CA_K;
 constexpr int CA_Q = 8;     // alpha values per transposed store
 
 // Each lane owns one (msky, ring) element and sums its 2M+1 values of C against the
@@ -61,16 +66,16 @@ struct alignas(64) Phase4 {
 };
 
 template <int QA>
-__global__ void __launch_bounds__(256) k_cube_alpha(const CubeArgs c, const double2* __restrict__ C,
+__global__ void __launch_bounds__(CA_NT) k_cube_alpha(const CubeArgs c, const double2* __restrict__ C,
                                                     const Phase4* __restrict__ E4, double2* __restrict__ P)
 {
     static_assert(QA % 4 == 0, "phases come in fours");
-    __shared__ double2 tile[CA_Q][CA_T][CA_T + 1];
+    __shared__ double2 tile[CA_Q][CA_K][CA_J + 1];
     const int nb = 2 * c.mbmax + 1;
     const int na4 = (c.nalpha + 3) / 4;     // Phase4 entries per mb row
     const int tid = threadIdx.x;
-    const int jj = tid & (CA_T - 1), kk = tid / CA_T;
-    const int j0 = blockIdx.x * CA_T, k0 = blockIdx.y * CA_T;
+    const int jj = tid % CA_J, kk = tid / CA_J;
+    const int j0 = blockIdx.x * CA_J, k0 = blockIdx.y * CA_K;
     const int j = j0 + jj, k = k0 + kk;
     const int L1 = c.lmax + 1;
     const bool in = (j < c.nring_chunk) && (k <= c.lmax);
@@ -113,10 +118,10 @@ __global__ void __launch_bounds__(256) k_cube_alpha(const CubeArgs c, const doub
 #pragma unroll
             for (int q = 0; q < CA_Q; ++q) tile[q][kk][jj] = make_double2(ar[q0 + q], ai[q0 + q]);
             __syncthreads();
-            const int jw = tid / CA_T, kw = tid & (CA_T - 1);
+            const int jw = tid / CA_K, kw = tid % CA_K;
             if (j0 + jw < c.nring_chunk && k0 + kw <= c.lmax) {
                 for (int q = 0; q < CA_Q && a0 + q0 + q < c.nalpha; ++q)
-                    P[((size_t)(j0 + jw) * c.nalpha + (a0 + q0 + q)) * L1 + (k0 + kw)] = tile[q][kw][jw];
+                    P[((size_t)(j0 + jw) * c.nalpha + (a0 + q0 + q)) * c.prow + (k0 + kw)] = tile[q][kw][jw];
             }
             __syncthreads();
         }
@@ -172,8 +177,6 @@ __device__ __forceinline__ void dft_regs(double2 (&v)[R])
         }
     }
 }
-
-constexpr int CG_HMAX = 8192;   // largest half length (ngamma <= 16384)
 
 // LDS slot of element i: one pad slot per 16 elements, so that the first pass's
 // stride-16 stores (and every other pass's accesses) spread over the banks.
@@ -232,17 +235,17 @@ __device__ __forceinline__ double2 packed(double2 a, double2 b, double2 w)
 // forms F_{g + r H/R} for r < R from the row of P and transforms them in registers.
 // All of a lane's loads are issued before the first is used.  The result goes to LDS,
 // or, when this is the only pass, to the output row.
-template <int R, int HMAX>
+template <int R, int HMAX, int NT>
 __device__ __forceinline__ void first_pass(const double2* __restrict__ P, const double2* __restrict__ tw,
                                            int H, int N, int L, double2* X, double2* out, bool last)
 {
-    constexpr int GM = HMAX / (R * 256) > 0 ? HMAX / (R * 256) : 1;
+    constexpr int GM = HMAX / (R * NT) > 0 ? HMAX / (R * NT) : 1;
     const int tid = threadIdx.x;
     const int ng = H / R;
     double2 v[GM][R];
 #pragma unroll
     for (int i = 0; i < GM; ++i) {
-        const int g = tid + 256 * i;
+        const int g = tid + NT * i;
         if (g < ng) {
 #pragma unroll
             for (int r = 0; r < R; ++r) {
@@ -253,7 +256,7 @@ __device__ __forceinline__ void first_pass(const double2* __restrict__ P, const 
     }
 #pragma unroll
     for (int i = 0; i < GM; ++i) {
-        const int g = tid + 256 * i;
+        const int g = tid + NT * i;
         if (g < ng) {
             dft_regs<R>(v[i]);
             if (last) {
@@ -272,11 +275,11 @@ __device__ __forceinline__ void first_pass(const double2* __restrict__ P, const 
 // writes, barrier); HMAX bounds H, hence the groups a lane handles.  The last pass
 // (Ns = H / R, so each lane's outputs g + r Ns are contiguous across lanes) writes
 // the output row instead.
-template <int R, int HMAX, bool LAST>
+template <int R, int HMAX, int NT, bool LAST>
 __device__ __forceinline__ void stockham_pass(double2* X, int H, int Ns, int N, const double2* __restrict__ tw,
                                               double2* __restrict__ out)
 {
-    constexpr int GM = HMAX / (R * 256) > 0 ? HMAX / (R * 256) : 1;
+    constexpr int GM = HMAX / (R * NT) > 0 ? HMAX / (R * NT) : 1;
     const int tid = threadIdx.x;
     const int ng = H / R;
     const int step = N / (Ns * R);
@@ -284,12 +287,12 @@ __device__ __forceinline__ void stockham_pass(double2* X, int H, int Ns, int N, 
     // twiddle loads first (their latency overlaps the LDS reads and the barrier)
 #pragma unroll
     for (int i = 0; i < GM; ++i) {
-        const int g = tid + 256 * i;
+        const int g = tid + NT * i;
         if (g < ng) twiddle_base<R>(tw, (g & (Ns - 1)) * step, b[i]);
     }
 #pragma unroll
     for (int i = 0; i < GM; ++i) {
-        const int g = tid + 256 * i;
+        const int g = tid + NT * i;
         if (g < ng) {
 #pragma unroll
             for (int r = 0; r < R; ++r) v[i][r] = X[pad(g + r * ng)];
@@ -298,7 +301,7 @@ __device__ __forceinline__ void stockham_pass(double2* X, int H, int Ns, int N, 
     if (!LAST) __syncthreads();
 #pragma unroll
     for (int i = 0; i < GM; ++i) {
-        const int g = tid + 256 * i;
+        const int g = tid + NT * i;
         if (g < ng) {
             const int k = g & (Ns - 1);
             apply_twiddles<R>(v[i], b[i]);
@@ -316,13 +319,13 @@ __device__ __forceinline__ void stockham_pass(double2* X, int H, int Ns, int N, 
     if (!LAST) __syncthreads();
 }
 
-template <int HMAX>
-__global__ void __launch_bounds__(256) k_cube_gamma(const CubeArgs c)
+template <int HMAX, int NT>
+__global__ void __launch_bounds__(NT) k_cube_gamma(const CubeArgs c)
 {
     extern __shared__ double2 X[];   // pad(H) + 1 entries
     const int row = blockIdx.x;      // (ring within the chunk) * nalpha + alpha
     const int N = c.ngamma, H = N / 2, L = c.lmax;
-    const double2* P = reinterpret_cast<const double2*>(c.P) + (size_t)row * (L + 1);
+    const double2* P = reinterpret_cast<const double2*>(c.P) + (size_t)row * c.prow;
     const double2* tw = reinterpret_cast<const double2*>(c.tw);
     // f_n = c[2n] + i c[2n+1] is the length-H transform of F
     double2* out = reinterpret_cast<double2*>(c.cube) + ((size_t)c.ring0 * c.nalpha + row) * (size_t)H;
@@ -330,35 +333,41 @@ __global__ void __launch_bounds__(256) k_cube_gamma(const CubeArgs c)
     case 1:
         if (threadIdx.x == 0) out[0] = packed(half_spec(P, 0, N, L), half_spec(P, 1, N, L), tw[0]);
         return;
-    case 2: first_pass<2, HMAX>(P, tw, H, N, L, X, out, true); return;
-    case 4: first_pass<4, HMAX>(P, tw, H, N, L, X, out, true); return;
-    case 8: first_pass<8, HMAX>(P, tw, H, N, L, X, out, true); return;
+    case 2: first_pass<2, HMAX, NT>(P, tw, H, N, L, X, out, true); return;
+    case 4: first_pass<4, HMAX, NT>(P, tw, H, N, L, X, out, true); return;
+    case 8: first_pass<8, HMAX, NT>(P, tw, H, N, L, X, out, true); return;
     default: break;
     }
-    first_pass<16, HMAX>(P, tw, H, N, L, X, out, H == 16);
+    first_pass<16, HMAX, NT>(P, tw, H, N, L, X, out, H == 16);
     int Ns = 16, rem = H / 16;
-    while (rem > 16) { stockham_pass<16, HMAX, false>(X, H, Ns, N, tw, out); Ns *= 16; rem /= 16; }
-    if (rem == 16) stockham_pass<16, HMAX, true>(X, H, Ns, N, tw, out);
-    else if (rem == 8) stockham_pass<8, HMAX, true>(X, H, Ns, N, tw, out);
-    else if (rem == 4) stockham_pass<4, HMAX, true>(X, H, Ns, N, tw, out);
-    else if (rem == 2) stockham_pass<2, HMAX, true>(X, H, Ns, N, tw, out);
+    while (rem > 16) { stockham_pass<16, HMAX, NT, false>(X, H, Ns, N, tw, out); Ns *= 16; rem /= 16; }
+    if (rem == 16) stockham_pass<16, HMAX, NT, true>(X, H, Ns, N, tw, out);
+    else if (rem == 8) stockham_pass<8, HMAX, NT, true>(X, H, Ns, N, tw, out);
+    else if (rem == 4) stockham_pass<4, HMAX, NT, true>(X, H, Ns, N, tw, out);
+    else if (rem == 2) stockham_pass<2, HMAX, NT, true>(X, H, Ns, N, tw, out);
 }
 
 }  // namespace
 
+// The gamma pass's builds: (half length up to, lanes), one radix-16 group of the first pass per lane at the
+// largest half length, two at 8192.  With 256 lanes for every length half of them or more had no group at
+// 2048 and below, and still held registers: 1.06 ms instead of 0.84 at half length 2048 (2000 x 29 rows),
+// and 0.64 instead of 0.56 the call at half length 1024 (2000 x 19 rows, lmax 1000) with twice the lanes.
+#define TC_CUBE_GAMMA(G) G(1024, 64) G(2048, 128) G(4096, 256) G(8192, 256)
+
 int launch_cube_alpha(const CubeArgs& c, void* stream)
 {
     hipStream_t s = (hipStream_t)stream;
-    dim3 g1((c.nring_chunk + CA_T - 1) / CA_T, (c.lmax + 1 + CA_T - 1) / CA_T);
+    dim3 g1((c.nring_chunk + CA_J - 1) / CA_J, (c.lmax + 1 + CA_K - 1) / CA_K);
     const double2* C = reinterpret_cast<const double2*>(c.C);
     const Phase4* E = reinterpret_cast<const Phase4*>(c.phase);
     double2* P = reinterpret_cast<double2*>(c.P);
     if (c.nalpha <= 8)
-        hipLaunchKernelGGL(k_cube_alpha<8>, g1, dim3(256), 0, s, c, C, E, P);
+        hipLaunchKernelGGL(k_cube_alpha<8>, g1, dim3(CA_NT), 0, s, c, C, E, P);
     else if (c.nalpha <= 16)
-        hipLaunchKernelGGL(k_cube_alpha<16>, g1, dim3(256), 0, s, c, C, E, P);
+        hipLaunchKernelGGL(k_cube_alpha<16>, g1, dim3(CA_NT), 0, s, c, C, E, P);
     else
-        hipLaunchKernelGGL(k_cube_alpha<32>, g1, dim3(256), 0, s, c, C, E, P);
+        hipLaunchKernelGGL(k_cube_alpha<32>, g1, dim3(CA_NT), 0, s, c, C, E, P);
     return (int)hipGetLastError();
 }
 
@@ -367,21 +376,27 @@ int launch_cube_gamma(const CubeArgs& c, void* stream)
     hipStream_t s = (hipStream_t)stream;
     const int H = c.ngamma / 2;
     const size_t sh2 = sizeof(double2) * ((size_t)H + (H >> 4) + 1);
-    if (H <= 4096)
-        hipLaunchKernelGGL(k_cube_gamma<4096>, dim3(c.nring_chunk * c.nalpha), dim3(256), sh2, s, c);
-    else
-        hipLaunchKernelGGL(k_cube_gamma<CG_HMAX>, dim3(c.nring_chunk * c.nalpha), dim3(256), sh2, s, c);
-    return (int)hipGetLastError();
+    const int rows = c.nring_chunk * c.nalpha;
+#define G(hmax, nt)                                                                                       \
+    if (H <= hmax) {                                                                                      \
+        hipLaunchKernelGGL((k_cube_gamma<hmax, nt>), dim3(rows), dim3(nt), sh2, s, c);                    \
+        return (int)hipGetLastError();                                                                    \
+    }
+    TC_CUBE_GAMMA(G)
+#undef G
+    return (int)hipErrorInvalidValue;
 }
 
 int cube_set_lds_limits()
 {
     // the gamma pass needs up to (8192 + 512 + 1) * 16 bytes of LDS
-    int rc = (int)hipFuncSetAttribute((const void*)k_cube_gamma<4096>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      (4096 + 4096 / 16 + 1) * (int)sizeof(double2));
-    if (!rc)
-        rc = (int)hipFuncSetAttribute((const void*)k_cube_gamma<CG_HMAX>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                      (CG_HMAX + CG_HMAX / 16 + 1) * (int)sizeof(double2));
+    int rc = 0;
+#define G(hmax, nt)                                                                                          \
+    if (!rc)                                                                                                 \
+        rc = (int)hipFuncSetAttribute((const void*)k_cube_gamma<hmax, nt>, hipFuncAttributeMaxDynamicSharedMemorySize, \
+                                      (hmax + hmax / 16 + 1) * (int)sizeof(double2));
+    TC_CUBE_GAMMA(G)
+#undef G
     return rc;
 }
 

@@ -708,51 +708,58 @@ MatrixLayout make_matrix_layout(int l, int nring)
 
 // ---------------------------------------------------------------- data cube
 
-// Alpha sums held per ring chunk.  Two chunks are in flight: the alpha pass of one chunk runs
-// beside the FFTs of the chunk before.  (Chunks small enough for both to stay in the 256 MB
-// last-level cache, 64 rings at lmax 4096, lose more to the ramp of each launch than the cache
-// saves; from about 256 rings on the time no longer depends on the size.)
-constexpr size_t kCubeChunkBytes = (size_t)768 << 20;
+// Alpha sums held at a time.  The alpha pass of a chunk of rings and its FFTs run one after the other on the
+// call's stream: side by side (the FFTs of a chunk on a second stream, next to the alpha pass of the next) both
+// passes, bound by memory alone, took no less together, and two buffers left chunks of half the size.  Larger
+// chunks spend less on the ramps and tails of their launches: 2000 rings at lmax 2048 (1.9 GB of sums) take
+// 2.28 ms by 500 rings, 1.95 ms at once; 4000 at lmax 4096 8.43 ms by 500 and 7.85 ms at once.  (Chunks that
+// stay in the 256 MB last-level cache, 64 or 128 rings, lose far more to the ramps than the cache saves.)
+constexpr size_t kCubeSumBytes = (size_t)2 << 30;
+constexpr size_t kCubeOldSumBytes = (size_t)768 << 20;
 
 struct CubeLayout {
     size_t phase = 0, tw = 0, P = 0, total = 0;
-    size_t P_bytes = 0;   // one of the two P buffers
     int chunk = 0;        // rings per chunk
+    int prow = 0;         // row stride of P (complex)
 };
 
 int g_cube_chunk = 0;   // rings per chunk of the data cube (tc_set_tile); 0 = built-in
 
-CubeLayout make_cube_layout(int lmax, int mbmax, int nring, int nalpha, int ngamma)
+// P in bytes of at most `bytes`, its rows of `prow` entries, `buffers` chunks of it.
+CubeLayout cube_layout(int mbmax, int nring, int nalpha, int ngamma, int prow, size_t bytes, int buffers)
 {
     CubeLayout C;
-    const size_t per_ring = (size_t)16 * (size_t)nalpha * (size_t)(lmax + 1);
-    size_t chunk = std::max<size_t>(1, kCubeChunkBytes / per_ring);
+    C.prow = prow;
+    const size_t per_ring = (size_t)16 * (size_t)nalpha * (size_t)prow;
+    size_t chunk = std::max<size_t>(1, bytes / per_ring);
     if (chunk >= 16) chunk = chunk / 16 * 16;   // whole 16-ring tiles of the alpha pass
     if (g_cube_chunk > 0) chunk = (size_t)g_cube_chunk;
+    else if (buffers == 1 && chunk >= 16 && (size_t)nring > chunk) {   // chunks of equal size
+        const size_t n = ((size_t)nring + chunk - 1) / chunk;
+        chunk = (((size_t)nring + n - 1) / n + 15) / 16 * 16;
+    }
     C.chunk = (int)std::min<size_t>((size_t)nring, chunk);
     size_t off = 0;
     C.phase = off; off = align_up(off + (size_t)16 * ((nalpha + 3) / 4 * 4) * (2 * mbmax + 1));
     C.tw = off;    off = align_up(off + (size_t)16 * ngamma);
-    C.P_bytes = align_up(per_ring * (size_t)C.chunk);
-    C.P = off;     off += 2 * C.P_bytes;
+    C.P = off;     off += (size_t)buffers * align_up(per_ring * (size_t)C.chunk);
     C.total = off;
     return C;
 }
 
-// The second stream of the data cube on device dev (created on first use, default priority,
-// kept until the process ends); hipError_t value.
-int cube_side_stream(int dev, hipStream_t* s)
+// Rows of P padded to whole 128-byte lines: a store that ends inside a line is written as two partial ones.
+CubeLayout make_cube_layout(int lmax, int mbmax, int nring, int nalpha, int ngamma)
 {
-    static std::mutex mu;
-    static hipStream_t streams[64] = {};
-    if (dev < 0 || dev >= 64) return (int)hipErrorInvalidDevice;
-    std::lock_guard<std::mutex> lock(mu);
-    if (!streams[dev]) {
-        const int rc = (int)hipStreamCreateWithFlags(&streams[dev], hipStreamNonBlocking);
-        if (rc) return rc;
-    }
-    *s = streams[dev];
-    return 0;
+    return cube_layout(mbmax, nring, nalpha, ngamma, (lmax + 8) / 8 * 8, kCubeSumBytes, 1);
+}
+
+// The layout of a workspace of ws bytes.  One too small for make_cube_layout's, but of the size that was asked
+// for when two chunks of 768 MB were held, unpadded, takes such chunks.
+CubeLayout fit_cube_layout(int lmax, int mbmax, int nring, int nalpha, int ngamma, size_t ws)
+{
+    const CubeLayout C = make_cube_layout(lmax, mbmax, nring, nalpha, ngamma);
+    const CubeLayout old = cube_layout(mbmax, nring, nalpha, ngamma, lmax + 1, kCubeOldSumBytes, 2);
+    return ws < C.total && ws >= old.total ? old : C;
 }
 
 int check_cube(int lmax, int mbmax, int nring, int nalpha, int ngamma)
@@ -848,7 +855,7 @@ int totalconv_datacube(int lmax, int mbmax, int nring, const double* C, int nalp
     if (rc) return rc;
     if (!C || !cube) return fail(TC_EINVAL, "C or cube is NULL");
     if (!aligned16(C) || !aligned16(cube)) return fail(TC_EINVAL, "C and cube must be 16-byte aligned");
-    const CubeLayout CL = make_cube_layout(lmax, mbmax, nring, nalpha, ngamma);
+    const CubeLayout CL = fit_cube_layout(lmax, mbmax, nring, nalpha, ngamma, ws_bytes);
     if (ws_bytes < CL.total)
         return fail(TC_ENOMEM, "workspace of %zu bytes is smaller than the %zu bytes needed", ws_bytes, CL.total);
     if (!workspace) return fail(TC_EINVAL, "workspace is NULL");
@@ -888,40 +895,18 @@ int totalconv_datacube(int lmax, int mbmax, int nring, const double* C, int nalp
     c.phase = reinterpret_cast<const double*>(static_cast<char*>(workspace) + CL.phase);
     c.tw = reinterpret_cast<const double*>(static_cast<char*>(workspace) + CL.tw);
     c.cube = cube;
+    c.prow = CL.prow;
     if ((long long)CL.chunk * nalpha > 0x7fffffffLL) return fail(TC_EUNSUPPORTED, "data cube: too many rows in one launch");
-    // Chunk k: the alpha pass on `stream` into P buffer k mod 2, then the gamma pass on the
-    // library's second stream of this device; the alpha pass of chunk k + 2 waits for the gamma
-    // pass of chunk k (same buffer), the call's end waits for every gamma pass.
-    hipStream_t A = static_cast<hipStream_t>(stream), G = nullptr;
-    if ((rc = cube_side_stream(dev, &G))) return hip_fail(rc, "data cube: second stream");
-    hipEvent_t ev[5] = {};   // start, alpha done (x2), gamma done (x2)
-    for (hipEvent_t& e : ev)
-        if (!rc) rc = (int)hipEventCreateWithFlags(&e, hipEventDisableTiming);
-    auto release = [&] {
-        for (hipEvent_t e : ev)
-            if (e) (void)hipEventDestroy(e);   // released once their work completes
-    };
-    if (rc) { release(); return hip_fail(rc, "data cube: events"); }
-    const int nchunk = (nring + CL.chunk - 1) / CL.chunk;
+    c.P = reinterpret_cast<double*>(static_cast<char*>(workspace) + CL.P);
     rc = timed_launch(TC_OP_CUBE, stream, [&] {
-        int r = (int)hipEventRecord(ev[0], A);
-        if (!r) r = (int)hipStreamWaitEvent(G, ev[0], 0);
-        for (int k = 0; k < nchunk && !r; ++k) {
-            const int b = k & 1;
-            c.ring0 = k * CL.chunk;
+        int r = 0;
+        for (c.ring0 = 0; c.ring0 < nring && !r; c.ring0 += CL.chunk) {
             c.nring_chunk = std::min(CL.chunk, nring - c.ring0);
-            c.P = reinterpret_cast<double*>(static_cast<char*>(workspace) + CL.P + (size_t)b * CL.P_bytes);
-            if (k >= 2) r = (int)hipStreamWaitEvent(A, ev[3 + b], 0);
-            if (!r) r = tc::launch_cube_alpha(c, A);
-            if (!r) r = (int)hipEventRecord(ev[1 + b], A);
-            if (!r) r = (int)hipStreamWaitEvent(G, ev[1 + b], 0);
-            if (!r) r = tc::launch_cube_gamma(c, G);
-            if (!r) r = (int)hipEventRecord(ev[3 + b], G);
+            r = tc::launch_cube_alpha(c, stream);
+            if (!r) r = tc::launch_cube_gamma(c, stream);
         }
-        for (int b = 0; b < std::min(nchunk, 2) && !r; ++b) r = (int)hipStreamWaitEvent(A, ev[3 + b], 0);
         return r;
     });
-    release();
     return rc ? hip_fail(rc, "totalconv_datacube launch") : TC_OK;
 }
 

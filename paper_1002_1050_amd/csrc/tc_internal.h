@@ -127,7 +127,8 @@ struct CubeArgs {
     const double* C;       // [2M+1][L+1][nring] complex (totalconv_fwd output)
     const double* phase;   // [2M+1][nalpha rounded up to 4] complex, e^{-2 pi i mb a / nalpha} (pad: 0)
     const double* tw;      // [ngamma] complex, e^{-2 pi i m / ngamma}
-    double* P;             // [nring_chunk][nalpha][L+1] complex, alpha sums of the chunk
+    double* P;             // [nring_chunk][nalpha][prow] complex, alpha sums of the chunk
+    int prow;              // row stride of P: lmax + 1, or that rounded up to whole 128-byte lines
     double* cube;          // [nring][nalpha][ngamma] real
 };
 
