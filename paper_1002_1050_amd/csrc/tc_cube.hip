@@ -8,13 +8,13 @@
 // that c is real.
 //
 // Two passes over each chunk of rings, both bound by HBM bandwidth.  At lmax 2048, mbmax 14, 2000 rings,
-// 29 x 4096 angles (1.9 GB of C in, 1.9 GB of P out and in, 1.9 GB of cube out) they take 0.98 and 0.84 ms,
-// 3.9 and 4.5 TB/s of reads and writes together (2.53 ms before the rows of P were padded to whole lines, the
-// passes taken one after the other and the gamma pass given workgroups of the row's size; 1.90 ms the call now):
-//  1. k_cube_alpha: P[j][a][k] = sum_mb E[mb][a] C[mb][k][j] for k = msky >= 0 -- the
-//     short sum over mb, done directly with the host's phase table E (read into scalar
-//     registers, four phases per load), and the
-//     transpose from ring-fastest C to rows (ring, alpha) with msky fastest.
+// 29 x 4096 angles (1.9 GB of C in, 1.9 GB of P out and in, 1.9 GB of cube out) they take 0.93 and 0.85 ms,
+// 4.1 and 4.5 TB/s of reads and writes together (2.53 ms before the rows of P were padded to whole lines, the
+// passes taken one after the other and the gamma pass given workgroups of the row's size, the sum over mb over single values; 1.84 ms the call now):
+//  1. k_cube_alpha: P[j][a][k] = sum_mb e^{-i mb alpha_a} C[mb][k][j] for k = msky >= 0 -- the
+//     short sum over mb, done directly over pairs (mb, -mb) and (alpha, -alpha) with the host's
+//     table of phases, and the transpose from ring-fastest C to rows (ring, alpha) with msky
+//     fastest.
 //  2. k_cube_gamma: one workgroup per row turns P_0..P_L into the real row
 //     c[g] = Re P_0 + 2 Re sum_{k>=1} P_k e^{-2 pi i k g / N}: the Hermitian
 //     spectrum is folded into its half X_0..X_{N/2}, packed into one complex
@@ -52,27 +52,33 @@ __device__ __forceinline__ void store_stream(double2* p, double2 v)
 // lines: the rows of P are padded to lines).  Tiles of 16 x 32 or 32 x 16 with 512 lanes took 3 to 6% longer
 // (two workgroups' barriers per compute unit instead of four).
 constexpr int CA_J = 16, CA_K = 16, CA_NT = CA_J * CA_K;
-constexpr int CA_Q = 8;     // alpha values per transposed store
+constexpr int CA_S = 4;     // slots (8 values of alpha) per transposed store
+constexpr int CA_U = 4;     // values of |mb| whose C are in flight together
 
-// Each lane owns one (msky, ring) element and sums its 2M+1 values of C against the
-// phases of QA values of alpha.  The C values are loaded CA_U at a time (all in flight
-// together).  The phase table [mb][alpha] (alpha padded to a multiple of 4) is read with
-// uniform 64-byte loads, four phases at a time, so the phases arrive in scalar registers
-// and every C value feeds 4 QA fused multiply-adds without LDS traffic.
-constexpr int CA_U = 8;
-
+// Each lane owns one (msky, ring) element.  With c, s = cos, sin of 2 pi m q / nalpha,
+//   e^{-i theta} C_m + e^{i theta} C_{-m} = c S + s T,  S = C_m + C_{-m},  T = -i (C_m - C_{-m}),
+// and alpha nalpha - q takes the same with -s: so slot q keeps A = sum_m c S and B = sum_m s T, four FMAs per
+// |mb| for two values of alpha, and P_q = A + B, P_{nalpha-q} = A - B: one FMA where the sum term by term took
+// four.  At mbmax 14 and 29 alphas that hides the arithmetic behind the loads (0.98 -> 0.93 ms at 2000 rings
+// of lmax 2048, the call of 4000 rings at lmax 4096 8.00 -> 7.25 ms); at mbmax 25 and 66 alphas, where it was
+// the bound, the call takes 0.75 ms instead of 1.90 (1000 rings, lmax 512).  The second launch bound holds the
+// accumulators of 16 slots and 8 loads to two waves per SIMD; without it the compiler takes registers that
+// leave one, 1.01 ms.  Slot 0 holds alpha 0 and, for even nalpha, alpha nalpha / 2, whose phases are 1 and (-1)^m:
+// its A sums S over even m, its B over odd m.  The table [|mb|][slot] of (c, s) is read with uniform 64-byte
+// loads, four slots at a time, so the phases arrive in scalar registers.
 struct alignas(64) Phase4 {
     double2 v[4];
 };
 
-template <int QA>
-__global__ void __launch_bounds__(CA_NT) k_cube_alpha(const CubeArgs c, const double2* __restrict__ C,
+template <int QS>
+__global__ void __launch_bounds__(CA_NT, 2) k_cube_alpha(const CubeArgs c, const double2* __restrict__ C,
                                                     const Phase4* __restrict__ E4, double2* __restrict__ P)
 {
-    static_assert(QA % 4 == 0, "phases come in fours");
-    __shared__ double2 tile[CA_Q][CA_K][CA_J + 1];
-    const int nb = 2 * c.mbmax + 1;
-    const int na4 = (c.nalpha + 3) / 4;     // Phase4 entries per mb row
+    static_assert(QS % 4 == 0 && QS % CA_S == 0, "phases come in fours");
+    __shared__ double2 tile[2 * CA_S][CA_K][CA_J + 1];
+    const int M = c.mbmax;
+    const int ns = (c.nalpha + 1) / 2;      // slots
+    const int ns4 = (ns + 3) / 4;           // Phase4 entries per row
     const int tid = threadIdx.x;
     const int jj = tid % CA_J, kk = tid / CA_J;
     const int j0 = blockIdx.x * CA_J, k0 = blockIdx.y * CA_K;
@@ -80,30 +86,40 @@ __global__ void __launch_bounds__(CA_NT) k_cube_alpha(const CubeArgs c, const do
     const int L1 = c.lmax + 1;
     const bool in = (j < c.nring_chunk) && (k <= c.lmax);
     const size_t mb_stride = (size_t)L1 * c.nring;
-    for (int a0 = 0; a0 < c.nalpha; a0 += QA) {
-        double ar[QA], ai[QA];
+    for (int s0 = 0; s0 < ns; s0 += QS) {
+        double ax[QS], ay[QS], bx[QS], by[QS];
 #pragma unroll
-        for (int q = 0; q < QA; ++q) { ar[q] = 0.0; ai[q] = 0.0; }
+        for (int q = 0; q < QS; ++q) { ax[q] = 0.0; ay[q] = 0.0; bx[q] = 0.0; by[q] = 0.0; }
         if (in) {
-            const double2* src = C + (size_t)k * c.nring + (c.ring0 + j);
-            for (int mb0 = 0; mb0 < nb; mb0 += CA_U) {
-                double2 v[CA_U];
-#pragma unroll
-                for (int u = 0; u < CA_U; ++u)
-                    v[u] = (mb0 + u < nb) ? src[(size_t)(mb0 + u) * mb_stride] : make_double2(0.0, 0.0);
+            const double2* src = C + (size_t)M * mb_stride + (size_t)k * c.nring + (c.ring0 + j);
+            for (int m0 = 0; m0 <= M; m0 += CA_U) {
+                double2 vp[CA_U], vm[CA_U];
 #pragma unroll
                 for (int u = 0; u < CA_U; ++u) {
-                    if (mb0 + u < nb) {
-                        const Phase4* row = E4 + (size_t)(mb0 + u) * na4 + a0 / 4;
+                    const int m = m0 + u;
+                    vp[u] = m <= M ? src[(size_t)m * mb_stride] : make_double2(0.0, 0.0);
+                    vm[u] = m > 0 && m <= M ? *(src - (size_t)m * mb_stride) : make_double2(0.0, 0.0);
+                }
 #pragma unroll
-                        for (int q4 = 0; q4 < QA / 4; ++q4) {
-                            if (a0 + 4 * q4 < c.nalpha) {
+                for (int u = 0; u < CA_U; ++u) {
+                    const int m = m0 + u;
+                    if (m <= M) {
+                        const double2 S = cadd(vp[u], vm[u]);
+                        const double2 T = m > 0 ? make_double2(vp[u].y - vm[u].y, vm[u].x - vp[u].x)
+                                                : make_double2(0.0, 0.0);
+                        const double2 T0 = s0 == 0 ? S : T;
+                        const Phase4* row = E4 + (size_t)m * ns4 + s0 / 4;
+#pragma unroll
+                        for (int q4 = 0; q4 < QS / 4; ++q4) {
+                            if (s0 + 4 * q4 < ns) {
                                 const Phase4 e = row[q4];
 #pragma unroll
                                 for (int i = 0; i < 4; ++i) {
                                     const int q = 4 * q4 + i;
-                                    ar[q] = fma(e.v[i].x, v[u].x, fma(-e.v[i].y, v[u].y, ar[q]));
-                                    ai[q] = fma(e.v[i].x, v[u].y, fma(e.v[i].y, v[u].x, ai[q]));
+                                    ax[q] = fma(e.v[i].x, S.x, ax[q]);
+                                    ay[q] = fma(e.v[i].x, S.y, ay[q]);
+                                    bx[q] = fma(e.v[i].y, q ? T.x : T0.x, bx[q]);
+                                    by[q] = fma(e.v[i].y, q ? T.y : T0.y, by[q]);
                                 }
                             }
                         }
@@ -111,17 +127,24 @@ __global__ void __launch_bounds__(CA_NT) k_cube_alpha(const CubeArgs c, const do
                 }
             }
         }
-        // transposed stores, CA_Q values of alpha at a time: lanes with consecutive msky
+        // transposed stores, CA_S slots at a time: lanes with consecutive msky
 #pragma unroll
-        for (int q0 = 0; q0 < QA; q0 += CA_Q) {
-            if (a0 + q0 >= c.nalpha) break;
+        for (int q0 = 0; q0 < QS; q0 += CA_S) {
+            if (s0 + q0 >= ns) break;
 #pragma unroll
-            for (int q = 0; q < CA_Q; ++q) tile[q][kk][jj] = make_double2(ar[q0 + q], ai[q0 + q]);
+            for (int q = 0; q < CA_S; ++q) {
+                tile[2 * q][kk][jj] = make_double2(ax[q0 + q] + bx[q0 + q], ay[q0 + q] + by[q0 + q]);
+                tile[2 * q + 1][kk][jj] = make_double2(ax[q0 + q] - bx[q0 + q], ay[q0 + q] - by[q0 + q]);
+            }
             __syncthreads();
             const int jw = tid / CA_K, kw = tid % CA_K;
             if (j0 + jw < c.nring_chunk && k0 + kw <= c.lmax) {
-                for (int q = 0; q < CA_Q && a0 + q0 + q < c.nalpha; ++q)
-                    P[((size_t)(j0 + jw) * c.nalpha + (a0 + q0 + q)) * c.prow + (k0 + kw)] = tile[q][kw][jw];
+                double2* row = P + (size_t)(j0 + jw) * c.nalpha * c.prow + (k0 + kw);
+                for (int q = 0; q < CA_S && s0 + q0 + q < ns; ++q) {
+                    const int a = s0 + q0 + q, other = a ? c.nalpha - a : c.nalpha % 2 ? 0 : c.nalpha / 2;
+                    row[(size_t)a * c.prow] = tile[2 * q][kw][jw];
+                    if (other) row[(size_t)other * c.prow] = tile[2 * q + 1][kw][jw];
+                }
             }
             __syncthreads();
         }
@@ -363,11 +386,11 @@ int launch_cube_alpha(const CubeArgs& c, void* stream)
     const Phase4* E = reinterpret_cast<const Phase4*>(c.phase);
     double2* P = reinterpret_cast<double2*>(c.P);
     if (c.nalpha <= 8)
-        hipLaunchKernelGGL(k_cube_alpha<8>, g1, dim3(CA_NT), 0, s, c, C, E, P);
+        hipLaunchKernelGGL(k_cube_alpha<4>, g1, dim3(CA_NT), 0, s, c, C, E, P);
     else if (c.nalpha <= 16)
-        hipLaunchKernelGGL(k_cube_alpha<16>, g1, dim3(CA_NT), 0, s, c, C, E, P);
+        hipLaunchKernelGGL(k_cube_alpha<8>, g1, dim3(CA_NT), 0, s, c, C, E, P);
     else
-        hipLaunchKernelGGL(k_cube_alpha<32>, g1, dim3(CA_NT), 0, s, c, C, E, P);
+        hipLaunchKernelGGL(k_cube_alpha<16>, g1, dim3(CA_NT), 0, s, c, C, E, P);
     return (int)hipGetLastError();
 }
 

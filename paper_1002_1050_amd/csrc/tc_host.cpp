@@ -740,7 +740,7 @@ CubeLayout cube_layout(int mbmax, int nring, int nalpha, int ngamma, int prow, s
     }
     C.chunk = (int)std::min<size_t>((size_t)nring, chunk);
     size_t off = 0;
-    C.phase = off; off = align_up(off + (size_t)16 * ((nalpha + 3) / 4 * 4) * (2 * mbmax + 1));
+    C.phase = off; off = align_up(off + (size_t)16 * ((nalpha + 3) / 4 * 4) * (2 * mbmax + 1));   // half is used
     C.tw = off;    off = align_up(off + (size_t)16 * ngamma);
     C.P = off;     off += (size_t)buffers * align_up(per_ring * (size_t)C.chunk);
     C.total = off;
@@ -871,17 +871,21 @@ int totalconv_datacube(int lmax, int mbmax, int nring, const double* C, int nalp
     if (need > (size_t)lds_max)
         return fail(TC_EUNSUPPORTED, "data cube needs %zu bytes of LDS per workgroup, the device allows %d", need,
                     lds_max);
-    // tables: e^{-2 pi i mb a / nalpha} ([mb][a]) and e^{-2 pi i m / ngamma}, in long double, rounded once
+    // tables: (cos, sin)(2 pi m q / nalpha) ([m][slot q], rows padded with zeros to whole groups of 4; slot 0,
+    // alphas 0 and nalpha / 2: 1 for the sum that m belongs to) and e^{-2 pi i m / ngamma}, in long double,
+    // rounded once
     std::vector<char> img(CL.P, 0);
     double* ph = reinterpret_cast<double*>(img.data() + CL.phase);
-    const size_t na4 = (size_t)(nalpha + 3) / 4 * 4;   // rows padded to whole groups of 4 (zeros)
-    for (int a = 0; a < nalpha; ++a)
-        for (int mb = -mbmax; mb <= mbmax; ++mb) {
-            const long long m = (((long long)mb * a) % nalpha + nalpha) % nalpha;
-            const ld ang = 2.0L * kPiL * (ld)m / (ld)nalpha;
-            ph[2 * ((size_t)(mb + mbmax) * na4 + a)] = (double)cosl(ang);
-            ph[2 * ((size_t)(mb + mbmax) * na4 + a) + 1] = (double)-sinl(ang);
+    const int nslot = (nalpha + 1) / 2;
+    for (int m = 0; m <= mbmax; ++m) {
+        double* row = ph + 2 * (size_t)m * ((nslot + 3) / 4 * 4);
+        row[m & 1] = 1.0;
+        for (int q = 1; q < nslot; ++q) {
+            const ld ang = 2.0L * kPiL * (ld)((long long)m * q % nalpha) / (ld)nalpha;
+            row[2 * q] = (double)cosl(ang);
+            row[2 * q + 1] = (double)sinl(ang);
         }
+    }
     double* tw = reinterpret_cast<double*>(img.data() + CL.tw);
     for (int m = 0; m < ngamma; ++m) {
         const ld ang = 2.0L * kPiL * (ld)m / (ld)ngamma;

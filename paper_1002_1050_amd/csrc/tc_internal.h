@@ -125,7 +125,7 @@ struct CubeArgs {
     int lmax, mbmax, nring, nalpha, ngamma;
     int ring0, nring_chunk;
     const double* C;       // [2M+1][L+1][nring] complex (totalconv_fwd output)
-    const double* phase;   // [2M+1][nalpha rounded up to 4] complex, e^{-2 pi i mb a / nalpha} (pad: 0)
+    const double* phase;   // [M+1][(nalpha+1)/2 rounded up to 4] (cos, sin) of the alpha pass (pad: 0)
     const double* tw;      // [ngamma] complex, e^{-2 pi i m / ngamma}
     double* P;             // [nring_chunk][nalpha][prow] complex, alpha sums of the chunk
     int prow;              // row stride of P: lmax + 1, or that rounded up to whole 128-byte lines
