@@ -1,8 +1,8 @@
 """Tile autotuner: picks (R, TB, TR) for plain calls and batched plans.
 
-R is the chain block (chains per lane; a workgroup covers 256 R ring slots of a
-column), TB the l block (values of l per LDS coefficient block), TR the
-adjoint's reduction block (steps per wave reduction).
+R is the chain block (chains per lane; a workgroup covers up to 256 R ring slots of a
+column), TB the l block of the adjoint's sums, TR the third of the triple (value 4; no
+kernel depends on it).
 
 Each candidate runs the real launch (after one untimed warm-up) and is timed with
 HIP events on the stream it runs on; the fastest wins.  Results are cached in a
