@@ -69,12 +69,11 @@ def _bytes(fetch_kib, write_kib, copy_fetch_kib, copy_write_kib=2097152.0):
 MEASURED_TRAFFIC = {
     # FETCH_SIZE and WRITE_SIZE of the kernels as built from this source, each scaled by the
     # counts of a 2 GiB device-to-device copy in the same run
-    "kernel_source_sha256": ["accdb2a8b4aad6c420f4213ccefc993ad46b38da8747be5129beade2de1ad0ee"],
+    "kernel_source_sha256": ["7f9c880f125db3c99ea17aa1de918ed0a079031ef24de29f64847ca951690520"],
     "lmax4096": {
         # the forward: its two launches, k_fwd_rows and k_fwd, together
-        "k_fwd": {"8,64,4": _bytes(1449012.8 + 3725.5, 16475947.9 + 0.0, 1048611.6),
-                  "4,64,4": _bytes(973078.5 + 3726.5, 16633820.6 + 0.0, 1048611.6)},
-        "k_adj": {"8,64,4": _bytes(11091143.9, 17801268.9, 1048611.6)},
+        "k_fwd": {"8,64,4": _bytes(1336062.8 + 3726.5, 19877223.4 + 0.0, 1048610.3)},
+        "k_adj": {"8,64,4": _bytes(12585714.5, 20676724.6, 1048610.3)},
     },
 }
 
