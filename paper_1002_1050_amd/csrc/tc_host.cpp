@@ -54,6 +54,13 @@ size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
+// Whether two arrays of `bytes` share memory.
+bool overlap(const void* p, const void* q, size_t bytes)
+{
+    const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+    return a < b ? b - a < bytes : a - b < bytes;
+}
+
 typedef long double ld;
 
 void split_dd(ld v, double& hi, double& lo)
@@ -683,6 +690,17 @@ int adj_impl(int lmax, int mbmax, int nring, const double* cosbeta, int npair, c
             e.alm_bar = (alm_bar && !sky_shared) ? alm_bar[p] : nullptr;
             e.blm_bar = blm_bar ? blm_bar[p] : nullptr;
             e.beam_sym = a.beam_sym;
+            // One launch forms both gradients side by side.  A gradient written over its input (blm_bar over
+            // blm, which the sky gradient reads; alm_bar over alm, which the beam gradient reads) takes the
+            // two one after the other, the sky gradient first.
+            const size_t beam_bytes = (size_t)16 * (2 * mbmax + 1) * (lmax + 1), sky_bytes = (size_t)16 * L.P;
+            if (e.alm_bar && e.blm_bar &&
+                (overlap(e.blm_bar, e.blm, beam_bytes) || overlap(e.alm_bar, e.alm, sky_bytes))) {
+                tc::EpiArgs sky = e;
+                sky.blm_bar = nullptr;
+                if ((rc = tc::launch_adj_epilogue(sky, stream))) return hip_fail(rc, "totalconv_adj epilogue launch");
+                e.alm_bar = nullptr;
+            }
             if ((rc = tc::launch_adj_epilogue(e, stream))) return hip_fail(rc, "totalconv_adj epilogue launch");
         }
     }

@@ -1,0 +1,110 @@
+// What the entry points of libtotalconv enqueue, and how long the host memory behind it lives: tc_host.cpp
+// on the fake runtime of fake_hip.h, with launchers that record their arguments.  Run with the name of a
+// check; every statement prints, the program ends with "ok" and status 0, or status 1.
+#include "fake_hip.h"
+
+#include "../../paper_1002_1050_amd/csrc/tc_host.cpp"
+
+#include <cstdio>
+
+namespace {
+
+std::vector<tc::Tile> g_adj_tiles;
+std::vector<tc::EpiArgs> g_epilogues;
+
+}  // namespace
+
+namespace tc {
+int launch_matrix(const MatrixArgs&, int, void*) { return 0; }
+int matrix_rows_per_group(int) { return 112; }
+int launch_cube_alpha(const CubeArgs&, void*) { return 0; }
+int launch_cube_gamma(const CubeArgs&, void*) { return 0; }
+int cube_set_lds_limits() { return 0; }
+int launch_wigner(const WignerArgs&, Tile, void*) { return 0; }
+int launch_fwd(const FwdArgs&, Tile, void*) { return 0; }
+int launch_beam_symmetry(const double*, int, int, int*, void*) { return 0; }
+int launch_adj(const AdjArgs&, Tile t, void*) { g_adj_tiles.push_back(t); return 0; }
+int launch_prep(const PrepArgs& a, void* s)
+{
+    if (a.bytes) fake::enqueue(s, [=] { std::memcpy(a.dst, a.src, a.bytes); });
+    return 0;
+}
+int launch_adj_epilogue(const EpiArgs& e, void*) { g_epilogues.push_back(e); return 0; }
+int launch_adj_sky_pairs(const EpiPairsArgs&, void*) { return 0; }
+int launch_fwd_items(const FwdArgs*, const int*, int, Tile, void*) { return 0; }
+int fwd_walk_pairs(Tile t) { return t.R >= 8 ? 2 : 4; }
+int adj_walk_pairs_of(Tile t) { return (t.R <= 4 && t.TB <= 32) ? 2 : 1; }
+int launch_adj_items(const AdjArgs*, const int*, int, Tile t, void*) { g_adj_tiles.push_back(t); return 0; }
+int launch_adj_sky_multi(const EpiArgs*, int, int, bool, double*, void*) { return 0; }
+int launch_adj_beam(const EpiArgs&, void*) { return 0; }
+bool tile_supported(int, Tile) { return true; }
+}  // namespace tc
+
+namespace {
+
+int g_failed = 0;
+
+void check(bool ok, const char* what)
+{
+    std::printf("%s %s\n", ok ? "pass" : "FAIL", what);
+    std::fflush(stdout);
+    if (!ok) g_failed = 1;
+}
+
+std::vector<double> grid(int n)
+{
+    std::vector<double> b(n);
+    for (int j = 0; j < n; ++j) b[j] = (double)((j + 0.5L) * kPiL / n);
+    return b;
+}
+
+// Memory on a boundary of kAlign, as a device allocation has.
+struct Buffer {
+    explicit Buffer(size_t n) : p(std::aligned_alloc(kAlign, align_up(n))) { std::memset(p, 0, n); }
+    ~Buffer() { std::free(p); }
+    double* d() const { return static_cast<double*>(p); }
+    void* p;
+};
+
+// ------------------------------------------------------------------ gradients written over inputs
+// Both gradients in one launch run side by side: only where neither is written over what the other reads.
+void gradient_order()
+{
+    const int lmax = 12, mbmax = 3, nring = 9;
+    const std::vector<double> beta = grid(nring);
+    const size_t na = 16 * (lmax + 1) * (lmax + 2) / 2, nb = 16 * (2 * mbmax + 1) * (lmax + 1);
+    Buffer alm(na), blm(nb), C((size_t)nb * nring), ab(na), bb(nb);
+    const size_t ws = totalconv_workspace_bytes(TC_OP_ADJ, lmax, mbmax, nring);
+    Buffer w(ws);
+    auto adj = [&](double* a, double* b) {
+        g_epilogues.clear();
+        return totalconv_adj(lmax, mbmax, nring, beta.data(), alm.d(), blm.d(), C.d(), a, b, w.p, ws, nullptr);
+    };
+    auto two = [&] {   // the sky gradient's launch, then the beam gradient's
+        return g_epilogues.size() == 2 && g_epilogues[0].alm_bar && !g_epilogues[0].blm_bar && !g_epilogues[1].alm_bar &&
+               g_epilogues[1].blm_bar;
+    };
+    check(adj(ab.d(), bb.d()) == TC_OK && g_epilogues.size() == 1 && g_epilogues[0].alm_bar && g_epilogues[0].blm_bar,
+          "gradients beside their inputs: one launch");
+    check(adj(ab.d(), blm.d()) == TC_OK && two(), "blm_bar over blm: the sky gradient has read it before");
+    check(adj(alm.d(), bb.d()) == TC_OK && two(), "alm_bar over alm: the sky gradient first");
+    Buffer wide(2 * nb);
+    g_epilogues.clear();
+    check(totalconv_adj(lmax, mbmax, nring, beta.data(), alm.d(), wide.d() + 2, C.d(), ab.d(), wide.d(), w.p, ws,
+                        nullptr) == TC_OK && two(),
+          "blm_bar over a part of blm");
+    check(adj(nullptr, blm.d()) == TC_OK && g_epilogues.size() == 1, "the beam gradient alone");
+    hipDeviceSynchronize();
+}
+
+}  // namespace
+
+int main(int argc, char** argv)
+{
+    const std::string which = argc > 1 ? argv[1] : "";
+    if (which == "gradient_order") gradient_order();
+    else check(false, "unknown check");
+    if (g_failed) return 1;
+    std::printf("ok\n");
+    return 0;
+}
