@@ -41,7 +41,11 @@
  *   the workspace on that stream; the library keeps their host images for the
  *   calls of recent shapes and ring sets (at most 64, 1 GiB in all) in pinned
  *   memory it allocates and frees itself, so that a repeated call only enqueues
- *   that copy.  Buffers must stay valid until the stream has passed the call.
+ *   that copy.  A call captured into a graph reads its image on every replay: the
+ *   graph, and every executable graph made from it, keeps that image.  (A first
+ *   call of a shape allocates pinned memory, which a capture may not allow: make
+ *   it before the capture.)  Buffers must stay valid until the stream has passed
+ *   the call, of a captured call as long as its graph may be launched.
  * - Return value 0 on success, otherwise one of the negative TC_E* codes;
  *   tc_last_error() returns a message for the calling thread's last failure.
  *   Invalid arguments are rejected before any GPU work is enqueued.

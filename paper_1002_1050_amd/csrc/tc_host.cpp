@@ -14,6 +14,7 @@
 #include <hip/hip_runtime_api.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdint>
@@ -21,6 +22,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <list>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -414,30 +416,110 @@ int upload(void* ws, const std::vector<char>& img, void* stream)
 // Host images of the per-call tables, kept in pinned memory for repeated calls with the same
 // (kind, sizes, tile, ring set, pair list) on the same device: a repeated call skips the long
 // double prep and the column sort, and its upload is a kernel that reads the mapped image (launch_prep).
-// Least recently used entries are dropped beyond kCacheEntries or kCacheBytes, after their last
-// upload has completed.  The images never change once built.
+// Least recently used entries are dropped beyond kCacheEntries or kCacheBytes; the memory of an image is
+// given back once nothing can read it: no graph that a call was captured into holds it, and the
+// device has been waited for (any stream may have its upload queued).  The images never change once built.
+struct HostImage {
+    int dev = 0;
+    void* pinned = nullptr;
+    void* mapped = nullptr;         // `pinned` as the device sees it
+    size_t bytes = 0;
+};
+typedef std::shared_ptr<HostImage> ImageRef;
+
 struct TableImage {
     std::vector<int> head;          // kind, device, lmax, mbmax / npair, nring, R, NT, bytes
     std::vector<double> x;          // ring cosines
     std::vector<int> pairs;         // (mb, msky) pairs of wigner_d_rings
-    void* pinned = nullptr;
-    void* mapped = nullptr;         // `pinned` as the device sees it
-    size_t bytes = 0;
-    hipEvent_t done = nullptr;      // recorded after the last upload from `pinned`
+    ImageRef image;
 };
 
 constexpr size_t kCacheEntries = 64;
 constexpr size_t kCacheBytes = (size_t)1 << 30;
 std::mutex g_cache_mu;
 std::list<TableImage> g_cache;      // front: most recently used
+std::vector<ImageRef> g_dropped;    // images out of the cache whose memory has not been given back yet
 
-void release_image(TableImage& e)
+// What a graph holds of a captured call: a user object of the graph and of the executable graphs made from
+// it, released with the last of them.  The release may come from any thread, inside any runtime call, and
+// must call nothing of the runtime: it hands the hold to the next upload (reap_graph_holds).
+struct GraphHold {
+    ImageRef image;
+    GraphHold* next = nullptr;
+};
+std::atomic<GraphHold*> g_released{nullptr};
+
+void release_graph_hold(void* p)
 {
-    // best effort at teardown and eviction: the copy that last read the image must be done
-    if (e.done) { (void)hipEventSynchronize(e.done); (void)hipEventDestroy(e.done); }
-    if (e.pinned) (void)hipHostFree(e.pinned);
-    e.done = nullptr;
-    e.pinned = nullptr;
+    GraphHold* h = static_cast<GraphHold*>(p);
+    h->next = g_released.load();
+    while (!g_released.compare_exchange_weak(h->next, h)) {}
+}
+
+// The graph that `stream` is being captured into, or null.
+hipGraph_t capturing_graph(void* stream)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    unsigned long long id = 0;
+    hipGraph_t g = nullptr;
+    const hipGraphNode_t* deps = nullptr;
+    size_t ndep = 0;
+    if (hipStreamGetCaptureInfo_v2((hipStream_t)stream, &st, &id, &g, &deps, &ndep) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    return st == hipStreamCaptureStatusActive ? g : nullptr;
+}
+
+// The graph, and every executable graph made from it, keeps what `hold` owns (hipError_t value).
+int hold_for_graph(hipGraph_t graph, std::unique_ptr<GraphHold> hold)
+{
+    hipUserObject_t u = nullptr;
+    int rc = (int)hipUserObjectCreate(&u, hold.get(), release_graph_hold, 1, hipUserObjectNoDestructorSync);
+    if (rc) return rc;
+    (void)hold.release();           // the user object's from here on
+    rc = (int)hipGraphRetainUserObject(graph, u, 1, hipGraphUserObjectMove);
+    if (rc) (void)hipUserObjectRelease(u, 1);
+    return rc;
+}
+
+// Drop a reference to an image; the last one leaves it to free_dropped.  Under g_cache_mu.
+void drop_image(ImageRef& r)
+{
+    if (r && r.use_count() == 1) g_dropped.push_back(std::move(r));
+    r.reset();
+}
+
+// Under g_cache_mu.
+void reap_graph_holds()
+{
+    if (!g_released.load(std::memory_order_relaxed)) return;
+    for (GraphHold* h = g_released.exchange(nullptr); h;) {
+        GraphHold* next = h->next;
+        drop_image(h->image);
+        delete h;
+        h = next;
+    }
+}
+
+// Give the dropped images' memory back, each once its device has finished all that was enqueued; one whose
+// device cannot be waited for stays for a later call.  Under g_cache_mu, not during a capture.
+void free_dropped()
+{
+    if (g_dropped.empty()) return;
+    int cur = 0, synced = -1;
+    if (hipGetDevice(&cur) != hipSuccess) return;
+    std::vector<ImageRef> keep;
+    for (ImageRef& r : g_dropped) {
+        if (synced != r->dev) {
+            const bool ok = (r->dev == cur || hipSetDevice(r->dev) == hipSuccess) && hipDeviceSynchronize() == hipSuccess;
+            if (r->dev != cur) (void)hipSetDevice(cur);
+            if (!ok) { (void)hipGetLastError(); keep.push_back(std::move(r)); continue; }
+            synced = r->dev;
+        }
+        (void)hipHostFree(r->pinned);
+    }
+    g_dropped.swap(keep);
 }
 
 bool same_key(const TableImage& e, const std::vector<int>& head, int nring, const double* x, int npair,
@@ -471,7 +553,9 @@ int upload_tables(int kind, int lmax, int mbmax_or_npair, int nring, const doubl
     int rc = (int)hipGetDevice(&dev);
     if (rc) return hip_fail(rc, "table upload: hipGetDevice");
     const std::vector<int> head = {kind, dev, lmax, mbmax_or_npair, nring, t.R, t.NT, (int)L.tables_end};
+    const hipGraph_t graph = capturing_graph(stream);
     std::lock_guard<std::mutex> lock(g_cache_mu);
+    reap_graph_holds();
     auto it = g_cache.begin();
     for (; it != g_cache.end(); ++it)
         if (same_key(*it, head, nring, x, npair, mb, ms)) break;
@@ -482,41 +566,48 @@ int upload_tables(int kind, int lmax, int mbmax_or_npair, int nring, const doubl
         e.head = head;
         e.x.assign(x, x + nring);
         for (int i = 0; i < npair; ++i) { e.pairs.push_back(mb[i]); e.pairs.push_back(ms[i]); }
-        e.bytes = img.size();
-        rc = (int)hipHostMalloc(&e.pinned, e.bytes, hipHostMallocDefault);
-        if (!rc) rc = (int)hipEventCreateWithFlags(&e.done, hipEventDisableTiming);
-        if (rc) {   // no pinned memory: upload from the pageable image, uncached
-            (void)hipGetLastError();
-            release_image(e);
+        e.image = std::make_shared<HostImage>();
+        e.image->dev = dev;
+        e.image->bytes = img.size();
+        if (hipHostMalloc(&e.image->pinned, e.image->bytes, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();   // no pinned memory: upload from the pageable image, uncached
             rc = upload(ws, img, stream);
             return rc ? rc : launch_signs(signs, stream);
         }
-        if (hipHostGetDevicePointer(&e.mapped, e.pinned, 0) != hipSuccess) {
+        if (hipHostGetDevicePointer(&e.image->mapped, e.image->pinned, 0) != hipSuccess) {
             (void)hipGetLastError();
-            e.mapped = nullptr;
+            e.image->mapped = nullptr;
         }
-        std::memcpy(e.pinned, img.data(), e.bytes);
+        std::memcpy(e.image->pinned, img.data(), img.size());
         g_cache.push_front(std::move(e));
         it = g_cache.begin();
-        size_t total = 0;
-        for (const TableImage& c : g_cache) total += c.bytes;
-        while (g_cache.size() > kCacheEntries || (g_cache.size() > 1 && total > kCacheBytes)) {
-            total -= g_cache.back().bytes;
-            release_image(g_cache.back());
-            g_cache.pop_back();
+        if (!graph) {   // during a capture nothing can be waited for: a later call drops entries
+            size_t total = 0;
+            for (const TableImage& c : g_cache) total += c.image->bytes;
+            while (g_cache.size() > kCacheEntries || (g_cache.size() > 1 && total > kCacheBytes)) {
+                total -= g_cache.back().image->bytes;
+                drop_image(g_cache.back().image);
+                g_cache.pop_back();
+            }
+            free_dropped();
         }
     } else if (it != g_cache.begin()) {
         g_cache.splice(g_cache.begin(), g_cache, it);
         it = g_cache.begin();
     }
-    if (tc::launch_prep && it->mapped) {
-        signs.src = it->mapped; signs.dst = ws; signs.bytes = it->bytes;
+    const HostImage& im = *it->image;
+    if (tc::launch_prep && im.mapped) {
+        signs.src = im.mapped; signs.dst = ws; signs.bytes = im.bytes;
         rc = tc::launch_prep(signs, stream);
         signs.npair = 0;
     } else {
-        rc = (int)hipMemcpyAsync(ws, it->pinned, it->bytes, hipMemcpyHostToDevice, (hipStream_t)stream);
+        rc = (int)hipMemcpyAsync(ws, im.pinned, im.bytes, hipMemcpyHostToDevice, (hipStream_t)stream);
     }
-    if (!rc) rc = (int)hipEventRecord(it->done, (hipStream_t)stream);
+    if (!rc && graph) {
+        std::unique_ptr<GraphHold> hold(new GraphHold);
+        hold->image = it->image;
+        rc = hold_for_graph(graph, std::move(hold));
+    }
     return rc ? hip_fail(rc, "table upload") : launch_signs(signs, stream);
 }
 

@@ -97,12 +97,105 @@ void gradient_order()
     hipDeviceSynchronize();
 }
 
+// ------------------------------------------------------------------ lifetime of the tables' host images
+struct Shapes {   // forward calls that differ in their rings, hence in their tables
+    static constexpr int lmax = 6, mbmax = 1;
+    Buffer alm{16 * 28}, blm{16 * 21}, C{16 * 21 * 400};
+    std::vector<std::unique_ptr<Buffer>> ws;
+    Buffer& fwd(int nring, void* stream)
+    {
+        const std::vector<double> beta = grid(nring);
+        const size_t n = totalconv_workspace_bytes(TC_OP_FWD, lmax, mbmax, nring);
+        ws.emplace_back(new Buffer(n));
+        check(totalconv_fwd(lmax, mbmax, nring, beta.data(), alm.d(), blm.d(), C.d(), ws.back()->p, n, stream) == TC_OK,
+              "call");
+        return *ws.back();
+    }
+    // enough other shapes for every earlier image to leave the cache
+    void evict(void* stream)
+    {
+        for (int k = 0; k < (int)kCacheEntries + 6; ++k) {
+            fwd(100 + k, stream);
+            fake::run_stream(stream);
+        }
+    }
+};
+
+bool same_tables(const Buffer& a, const Buffer& b, int nring)
+{
+    const std::vector<double> beta = grid(nring);
+    std::vector<double> x;
+    rings_from_beta(nring, beta.data(), x);
+    const Layout L = make_layout(TC_OP_FWD, Shapes::lmax, Shapes::mbmax, nring, x.data(), tc::Tile{2, 64, 32, 4});
+    return std::memcmp(a.p, b.p, L.tables_end) == 0;
+}
+
+// An image leaves the cache while a call on another stream than its last reader's has not read it yet.
+void image_streams()
+{
+    Shapes s;
+    hipStream_t a = nullptr, b = nullptr;
+    hipStreamCreateWithFlags(&a, 0);
+    hipStreamCreateWithFlags(&b, 0);
+    Buffer& first = s.fwd(9, a);    // queued, not run
+    Buffer& last = s.fwd(9, b);
+    fake::run_stream(b);
+    s.evict(b);
+    fake::run_stream(a);
+    check(same_tables(first, last, 9), "the first stream's call read its tables");
+    check(fake::pinned().size() <= kCacheEntries, "images that left the cache are given back");
+    hipDeviceSynchronize();
+}
+
+// A captured call's image outlives the cache entry, as long as the executable graph, and no longer.
+void image_capture()
+{
+    Shapes s;
+    hipStream_t a = nullptr;
+    hipStreamCreateWithFlags(&a, 0);
+    Buffer& eager = s.fwd(9, a);
+    fake::run_stream(a);
+    hipStreamBeginCapture(a, hipStreamCaptureModeGlobal);
+    Buffer& captured = s.fwd(9, a);
+    hipGraph_t g = nullptr;
+    hipStreamEndCapture(a, &g);
+    hipGraphExec_t e = nullptr;
+    hipGraphInstantiate(&e, g, nullptr, nullptr, 0);
+    hipGraphDestroy(g);
+    for (int k = 0; k < 3; ++k) {
+        s.evict(nullptr);
+        std::memset(captured.p, 0, 64);
+        hipGraphLaunch(e, a);
+        fake::run_stream(a);
+        check(same_tables(captured, eager, 9), "a replay reads the tables");
+    }
+    check(fake::pinned().size() <= kCacheEntries + 1, "one image beside the cache");
+    hipGraphExecDestroy(e);
+    s.fwd(11, nullptr);
+    hipDeviceSynchronize();
+    s.evict(nullptr);
+    check(fake::pinned().size() <= kCacheEntries, "given back with the graph");
+    // a captured call on new rings: nothing leaves the cache during the capture
+    hipStreamBeginCapture(a, hipStreamCaptureModeRelaxed);
+    Buffer& fresh = s.fwd(17, a);
+    hipStreamEndCapture(a, &g);
+    hipGraphInstantiate(&e, g, nullptr, nullptr, 0);
+    s.evict(nullptr);
+    hipGraphLaunch(e, a);
+    fake::run_stream(a);
+    Buffer& again = s.fwd(17, nullptr);
+    hipDeviceSynchronize();
+    check(same_tables(fresh, again, 17), "new rings in a capture");
+}
+
 }  // namespace
 
 int main(int argc, char** argv)
 {
     const std::string which = argc > 1 ? argv[1] : "";
     if (which == "gradient_order") gradient_order();
+    else if (which == "image_streams") image_streams();
+    else if (which == "image_capture") image_capture();
     else check(false, "unknown check");
     if (g_failed) return 1;
     std::printf("ok\n");

@@ -1,0 +1,54 @@
+"""Calls captured into a HIP graph: after enough calls on other ring sets that the tables' host images
+have left the library's cache, and eager calls that overwrite the workspace, every replay equals
+the eager result bit for bit."""
+import pytest
+
+from paper_1002_1050_amd import synthetic as S
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1002_1050_amd import _binding
+    return _binding
+
+
+def dev(a):
+    return torch.from_numpy(a).to("cuda")
+
+
+def replays(B, name, call, fresh_rings=0):
+    """Eager result of call() (a list of tensors it writes), then three replays of it captured."""
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        want = [t.clone() for t in call()]
+        graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    print(f"[gpu] capture of {name}", flush=True)
+    with torch.cuda.graph(graph, stream=s):
+        out = call()
+    alm, blm = dev(S.sky_alm(12, 5)), dev(S.random_beam(12, 2, 6))
+    for k in range(3):
+        with torch.cuda.stream(s):
+            for n in range(fresh_rings):
+                B.totalconv_fwd(12, 2, S.ring_colatitudes(20 + 100 * k + n), alm, blm)
+            for t in out:
+                t.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(out, want):
+            assert torch.equal(a, b), f"replay {k} of {name}"
+
+
+def test_captured_convolution_after_eviction(B):
+    L, M, nring = 100, 3, 131
+    beta = S.ring_colatitudes(nring)
+    alm, blm, G = dev(S.sky_alm(L, 1)), dev(S.random_beam(L, M, 2)), dev(S.random_cbar(L, M, nring, 3))
+    replays(B, "totalconv_fwd", lambda: [B.totalconv_fwd(L, M, beta, alm, blm)], 70)
+    replays(B, "totalconv_adj", lambda: list(B.totalconv_adj(L, M, beta, alm, blm, G)), 70)
+    replays(B, "wigner_d_rings", lambda: [B.wigner_d_rings(L, [0, 2], [5, -7], beta)], 70)
