@@ -407,12 +407,6 @@ int check_ws(const Layout& L, void* ws, size_t ws_bytes)
     return TC_OK;
 }
 
-int upload(void* ws, const std::vector<char>& img, void* stream)
-{
-    const int rc = (int)hipMemcpyAsync(ws, img.data(), img.size(), hipMemcpyHostToDevice, (hipStream_t)stream);
-    return rc ? hip_fail(rc, "table upload (hipMemcpyAsync)") : TC_OK;
-}
-
 // Host images of the per-call tables, kept in pinned memory for repeated calls with the same
 // (kind, sizes, tile, ring set, pair list) on the same device: a repeated call skips the long
 // double prep and the column sort, and its upload is a kernel that reads the mapped image (launch_prep).
@@ -436,7 +430,7 @@ struct TableImage {
 
 constexpr size_t kCacheEntries = 64;
 constexpr size_t kCacheBytes = (size_t)1 << 30;
-std::mutex g_cache_mu;
+std::recursive_mutex g_cache_mu;   // upload_tables calls upload
 std::list<TableImage> g_cache;      // front: most recently used
 std::vector<ImageRef> g_dropped;    // images out of the cache whose memory has not been given back yet
 
@@ -445,6 +439,7 @@ std::vector<ImageRef> g_dropped;    // images out of the cache whose memory has 
 // must call nothing of the runtime: it hands the hold to the next upload (reap_graph_holds).
 struct GraphHold {
     ImageRef image;
+    std::vector<char> bytes;        // pageable tables (upload)
     GraphHold* next = nullptr;
 };
 std::atomic<GraphHold*> g_released{nullptr};
@@ -502,6 +497,22 @@ void reap_graph_holds()
     }
 }
 
+// Copy tables from pageable memory.  The copy has read them when hipMemcpyAsync returns, a captured one
+// reads them on every replay.
+int upload(void* ws, std::vector<char> img, void* stream)
+{
+    const hipGraph_t graph = capturing_graph(stream);
+    int rc = (int)hipMemcpyAsync(ws, img.data(), img.size(), hipMemcpyHostToDevice, (hipStream_t)stream);
+    if (!rc && graph) {
+        std::lock_guard<std::recursive_mutex> lock(g_cache_mu);
+        reap_graph_holds();
+        std::unique_ptr<GraphHold> hold(new GraphHold);
+        hold->bytes = std::move(img);
+        rc = hold_for_graph(graph, std::move(hold));
+    }
+    return rc ? hip_fail(rc, "table upload (hipMemcpyAsync)") : TC_OK;
+}
+
 // Give the dropped images' memory back, each once its device has finished all that was enqueued; one whose
 // device cannot be waited for stays for a later call.  Under g_cache_mu, not during a capture.
 void free_dropped()
@@ -554,7 +565,7 @@ int upload_tables(int kind, int lmax, int mbmax_or_npair, int nring, const doubl
     if (rc) return hip_fail(rc, "table upload: hipGetDevice");
     const std::vector<int> head = {kind, dev, lmax, mbmax_or_npair, nring, t.R, t.NT, (int)L.tables_end};
     const hipGraph_t graph = capturing_graph(stream);
-    std::lock_guard<std::mutex> lock(g_cache_mu);
+    std::lock_guard<std::recursive_mutex> lock(g_cache_mu);
     reap_graph_holds();
     auto it = g_cache.begin();
     for (; it != g_cache.end(); ++it)
@@ -571,7 +582,7 @@ int upload_tables(int kind, int lmax, int mbmax_or_npair, int nring, const doubl
         e.image->bytes = img.size();
         if (hipHostMalloc(&e.image->pinned, e.image->bytes, hipHostMallocDefault) != hipSuccess) {
             (void)hipGetLastError();   // no pinned memory: upload from the pageable image, uncached
-            rc = upload(ws, img, stream);
+            rc = upload(ws, std::move(img), stream);
             return rc ? rc : launch_signs(signs, stream);
         }
         if (hipHostGetDevicePointer(&e.image->mapped, e.image->pinned, 0) != hipSuccess) {
@@ -668,7 +679,7 @@ int fwd_impl(int op, int lmax, int mbmax, int nring, const double* cosbeta, int 
     } else {   // no pinned image: built here and copied from pageable host memory
         std::vector<char> img(L.tables_end, 0);
         build(img);
-        if (!(rc = upload(workspace, img, stream))) rc = launch_signs(signs, stream);
+        if (!(rc = upload(workspace, std::move(img), stream))) rc = launch_signs(signs, stream);
     }
     if (rc) return rc;
     tc::FwdArgs a{};
@@ -929,7 +940,7 @@ int wigner_d_matrix_x(int l, int nring, const double* cosbeta, double* d, void* 
         const ld v = 0.5L * (lgammal((ld)(2 * l + 1)) - lgammal((ld)(l + m + 1)) - lgammal((ld)(l - m + 1)));
         split_dd(v, lna[2 * m], lna[2 * m + 1]);
     }
-    if ((rc = upload(workspace, img, stream))) return rc;
+    if ((rc = upload(workspace, std::move(img), stream))) return rc;
     tc::MatrixArgs a{};
     a.l = l; a.nring = nring; a.ntile = ntile;
     a.ring = ring_ptrs(workspace, RL, nring);
@@ -1001,7 +1012,7 @@ int totalconv_datacube(int lmax, int mbmax, int nring, const double* C, int nalp
         tw[2 * m] = (double)cosl(ang);
         tw[2 * m + 1] = (double)-sinl(ang);
     }
-    if ((rc = upload(workspace, img, stream))) return rc;
+    if ((rc = upload(workspace, std::move(img), stream))) return rc;
     tc::CubeArgs c{};
     c.lmax = lmax; c.mbmax = mbmax; c.nring = nring; c.nalpha = nalpha; c.ngamma = ngamma;
     c.C = C;

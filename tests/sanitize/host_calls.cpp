@@ -188,6 +188,48 @@ void image_capture()
     check(same_tables(fresh, again, 17), "new rings in a capture");
 }
 
+// Tables that are copied from pageable memory: the calls without a cached image, captured.
+void pageable_capture()
+{
+    const int lmax = 8, mbmax = 1, nring = 5, nalpha = 3, ngamma = 16;
+    const std::vector<double> beta = grid(nring);
+    Buffer alm(16 * 45), blm(16 * 27), C(16 * 27 * nring), d(8 * 17 * 17 * nring), cube(8 * nring * nalpha * ngamma);
+    const size_t wm = wigner_d_matrix_workspace_bytes(lmax, nring);
+    const size_t wc = totalconv_datacube_workspace_bytes(lmax, mbmax, nring, nalpha, ngamma);
+    const size_t wf = totalconv_workspace_bytes(TC_OP_FWD, lmax, mbmax, nring);
+    const std::function<int(void*, hipStream_t)> calls[3] = {
+        [&](void* w, hipStream_t s) { return wigner_d_matrix(lmax, nring, beta.data(), d.d(), w, wm, s); },
+        [&](void* w, hipStream_t s) {
+            return totalconv_datacube(lmax, mbmax, nring, C.d(), nalpha, ngamma, cube.d(), w, wc, s);
+        },
+        [&](void* w, hipStream_t s) {
+            return tc::fwd_noalloc(lmax, mbmax, nring, beta.data(), alm.d(), blm.d(), C.d(), w, wf, s);
+        }};
+    const size_t bytes[3] = {wm, wc, wf};
+    const char* name[3] = {"wigner_d_matrix", "totalconv_datacube", "totalconv_fwd_noalloc"};
+    hipStream_t s = nullptr;
+    hipStreamCreateWithFlags(&s, 0);
+    for (int k = 0; k < 3; ++k) {
+        Buffer eager(bytes[k]), captured(bytes[k]);
+        check(calls[k](eager.p, s) == TC_OK, name[k]);
+        fake::run_stream(s);
+        hipStreamBeginCapture(s, hipStreamCaptureModeGlobal);
+        check(calls[k](captured.p, s) == TC_OK, "captured");
+        hipGraph_t g = nullptr;
+        hipStreamEndCapture(s, &g);
+        hipGraphExec_t e = nullptr;
+        hipGraphInstantiate(&e, g, nullptr, nullptr, 0);
+        hipGraphDestroy(g);
+        for (int r = 0; r < 2; ++r) {
+            std::memset(captured.p, 0, bytes[k]);
+            hipGraphLaunch(e, s);
+            fake::run_stream(s);
+            check(std::memcmp(captured.p, eager.p, bytes[k]) == 0, "a replay copies the tables");
+        }
+        hipGraphExecDestroy(e);
+    }
+}
+
 }  // namespace
 
 int main(int argc, char** argv)
@@ -196,6 +238,7 @@ int main(int argc, char** argv)
     if (which == "gradient_order") gradient_order();
     else if (which == "image_streams") image_streams();
     else if (which == "image_capture") image_capture();
+    else if (which == "pageable_capture") pageable_capture();
     else check(false, "unknown check");
     if (g_failed) return 1;
     std::printf("ok\n");

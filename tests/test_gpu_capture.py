@@ -52,3 +52,18 @@ def test_captured_convolution_after_eviction(B):
     replays(B, "totalconv_fwd", lambda: [B.totalconv_fwd(L, M, beta, alm, blm)], 70)
     replays(B, "totalconv_adj", lambda: list(B.totalconv_adj(L, M, beta, alm, blm, G)), 70)
     replays(B, "wigner_d_rings", lambda: [B.wigner_d_rings(L, [0, 2], [5, -7], beta)], 70)
+
+
+def test_captured_calls_with_pageable_tables(B):
+    L, M, nring = 40, 3, 33
+    beta = S.ring_colatitudes(nring)
+    alm, blm, C = dev(S.sky_alm(L, 1)), dev(S.random_beam(L, M, 2)), dev(S.random_cbar(L, M, nring, 3))
+    out = torch.empty((2 * M + 1, L + 1, nring), dtype=torch.complex128, device="cuda")
+
+    def noalloc():
+        B.totalconv_fwd_noalloc(L, M, beta, alm, blm, out)
+        return [out]
+
+    replays(B, "totalconv_fwd_noalloc", noalloc, 3)
+    replays(B, "wigner_d_matrix", lambda: [B.wigner_d_matrix(L, beta)], 3)
+    replays(B, "totalconv_datacube", lambda: [B.totalconv_datacube(L, M, C, 5, 128)], 3)
