@@ -642,6 +642,16 @@ int check_grid(const Layout& L)
     return TC_OK;
 }
 
+// Work items of one launch.  A launch packet counts them in 32 bits; the runtime refuses 2^32 and lets a larger
+// product wrap (2^32 + 512 work items: no error, one workgroup of 512 runs), so larger calls take several launches.
+constexpr long long kGridItems = 0xffffffffLL;
+
+// The units (columns, pairs, rings, ...) one launch takes, each of `groups` workgroups of `lanes` lanes.
+int per_launch(long long groups, int lanes)
+{
+    return (int)std::max(1LL, std::min(0x7fffffffLL, kGridItems / lanes / groups));
+}
+
 // Forward for npair (sky, beam) pairs: one output per pair, or (sum) one output.
 int fwd_impl(int op, int lmax, int mbmax, int nring, const double* cosbeta, int npair, const double* const* alm,
              const double* const* blm, int sum, double* const* C, void* workspace, size_t ws_bytes, void* stream,
@@ -694,7 +704,17 @@ int fwd_impl(int op, int lmax, int mbmax, int nring, const double* cosbeta, int 
     for (int p = 0; p < npair; ++p) { a.alm[p] = alm[p]; a.blm[p] = blm[p]; a.pmbmax[p] = mbmax; }
     for (int c = 0; c < nout; ++c) a.C[c] = C[c];
     a.beam_sym[0] = signs.sym;
-    rc = timed_launch(op, stream, [&] { return tc::launch_fwd(a, t, stream); });
+    const tc::ColumnTables col = a.col;
+    const int step = per_launch(L.ntile, t.NT);
+    rc = timed_launch(op, stream, [&] {
+        int r = 0;
+        for (long long c0 = 0; c0 < L.ncol && !r; c0 += step) {
+            a.ncol = (int)std::min<long long>(step, L.ncol - c0);
+            a.col = tc::ColumnTables{col.mb + c0, col.ms + c0, col.lnA + 2 * c0};
+            r = tc::launch_fwd(a, t, stream);
+        }
+        return r;
+    });
     return rc ? hip_fail(rc, "totalconv_fwd launch") : TC_OK;
 }
 
@@ -947,7 +967,19 @@ int wigner_d_matrix_x(int l, int nring, const double* cosbeta, double* d, void* 
     a.trig = reinterpret_cast<const double*>(static_cast<char*>(workspace) + M.trig);
     a.lnA = reinterpret_cast<const double*>(static_cast<char*>(workspace) + M.lna);
     a.d = d;
-    rc = timed_launch(TC_OP_MATRIX, stream, [&] { return tc::launch_matrix(a, R, stream); });
+    const tc::MatrixArgs all = a;
+    const int step = per_launch(2LL * ntile, tc::kMatrixLanes);
+    rc = timed_launch(TC_OP_MATRIX, stream, [&] {
+        int r = 0;
+        for (long long j0 = 0; j0 < nring && !r; j0 += step) {
+            a.nring = (int)std::min<long long>(step, nring - j0);
+            a.ring = tc::RingTables{all.ring.x + j0, all.ring.lch + j0, all.ring.lcl + j0, all.ring.lsh + j0, all.ring.lsl + j0};
+            a.trig = all.trig + 2 * j0;
+            a.d = all.d + j0 * (2LL * l + 1) * (2LL * l + 1);
+            r = tc::launch_matrix(a, R, stream);
+        }
+        return r;
+    });
     return rc ? hip_fail(rc, "wigner_d_matrix launch") : TC_OK;
 }
 
@@ -1022,10 +1054,12 @@ int totalconv_datacube(int lmax, int mbmax, int nring, const double* C, int nalp
     c.prow = CL.prow;
     if ((long long)CL.chunk * nalpha > 0x7fffffffLL) return fail(TC_EUNSUPPORTED, "data cube: too many rows in one launch");
     c.P = reinterpret_cast<double*>(static_cast<char*>(workspace) + CL.P);
+    const int step = std::min(CL.chunk, per_launch(nalpha, 256));   // a gamma workgroup per row, of up to 256 lanes
     rc = timed_launch(TC_OP_CUBE, stream, [&] {
         int r = 0;
-        for (c.ring0 = 0; c.ring0 < nring && !r; c.ring0 += CL.chunk) {
-            c.nring_chunk = std::min(CL.chunk, nring - c.ring0);
+        for (long long j0 = 0; j0 < nring && !r; j0 += step) {
+            c.ring0 = (int)j0;
+            c.nring_chunk = (int)std::min<long long>(step, nring - j0);
             r = tc::launch_cube_alpha(c, stream);
             if (!r) r = tc::launch_cube_gamma(c, stream);
         }
@@ -1178,7 +1212,18 @@ int wigner_d_rings_x(int lmax, int npair, const int* mb, const int* msky, int nr
     a.ring = ring_ptrs(workspace, L, nring);
     a.col = col_ptrs(workspace, L);
     a.d = d;
-    rc = timed_launch(TC_OP_WIGNER, stream, [&] { return tc::launch_wigner(a, t, stream); });
+    const tc::WignerArgs all = a;
+    const int step = per_launch(L.ntile, t.NT);
+    rc = timed_launch(TC_OP_WIGNER, stream, [&] {
+        int r = 0;
+        for (long long i0 = 0; i0 < npair && !r; i0 += step) {
+            a.npair = (int)std::min<long long>(step, npair - i0);
+            a.col = tc::ColumnTables{all.col.mb + i0, all.col.ms + i0, all.col.lnA + 2 * i0};
+            a.d = all.d + i0 * (lmax + 1) * nring;
+            r = tc::launch_wigner(a, t, stream);
+        }
+        return r;
+    });
     return rc ? hip_fail(rc, "wigner_d_rings launch") : TC_OK;
 }
 
@@ -1683,9 +1728,10 @@ int tc_plan_create(void** plan, int op, int ndet, const tc_detector* dets, int l
             hipStream_t q = k == 0 ? cs : side[k - 1];
             if (k > 0) rc = (int)hipStreamWaitEvent(q, fork, 0);
             const Launch& l = launches[k];
-            if (!rc)
+            const tc::Tile& wt = groups[l.grp].tile;
+            for (long long i = 0, step = per_launch(1, wt.NT); i < l.n && !rc; i += step)
                 rc = tc::launch_fwd_items(reinterpret_cast<const tc::FwdArgs*>(dm + args_off),
-                                          d_items + 3 * (size_t)l.first, l.n, groups[l.grp].tile, q);
+                                          d_items + 3 * (size_t)(l.first + i), (int)std::min(step, l.n - i), wt, q);
             if (!rc && k > 0) rc = (int)hipEventRecord(evs[k - 1], q);
         }
         for (int k = 0; k < nside && !rc; ++k) rc = (int)hipStreamWaitEvent(cs, evs[k], 0);
@@ -1694,8 +1740,10 @@ int tc_plan_create(void** plan, int op, int ndet, const tc_detector* dets, int l
         const tc::EpiArgs* d_eg = reinterpret_cast<const tc::EpiArgs*>(dm + epi_off);
         for (size_t k = 0; k < launches.size() && !rc; ++k) {
             const Launch& l = launches[k];
-            rc = tc::launch_adj_items(reinterpret_cast<const tc::AdjArgs*>(dm + args_off), d_items + 2 * (size_t)l.first,
-                                      l.n, groups[l.grp].tile, cs);
+            const tc::Tile& wt = groups[l.grp].tile;
+            for (long long i = 0, step = per_launch(1, wt.NT); i < l.n && !rc; i += step)
+                rc = tc::launch_adj_items(reinterpret_cast<const tc::AdjArgs*>(dm + args_off),
+                                          d_items + 2 * (size_t)(l.first + i), (int)std::min(step, l.n - i), wt, cs);
             if (!rc) rc = (int)hipEventRecord(evs[k], cs);
             if (!rc) rc = (int)hipStreamWaitEvent(es, evs[k], 0);
             if (!rc && alm_bar)

@@ -117,6 +117,7 @@ struct MatrixArgs {
     double* d;             // [nring][2l+1][2l+1], d[j][m+l][m'+l]
 };
 
+constexpr int kMatrixLanes = 512;   // lanes per workgroup
 int launch_matrix(const MatrixArgs& a, int variant, void* stream);
 int matrix_rows_per_group(int variant);   // rows m one workgroup walks (0: no such variant)
 

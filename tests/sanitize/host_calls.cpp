@@ -11,16 +11,19 @@ namespace {
 
 std::vector<tc::Tile> g_adj_tiles;
 std::vector<tc::EpiArgs> g_epilogues;
+std::vector<tc::MatrixArgs> g_matrix;
+std::vector<tc::WignerArgs> g_wigner;
+std::vector<tc::CubeArgs> g_alpha, g_gamma;
 
 }  // namespace
 
 namespace tc {
-int launch_matrix(const MatrixArgs&, int, void*) { return 0; }
+int launch_matrix(const MatrixArgs& a, int, void*) { g_matrix.push_back(a); return 0; }
 int matrix_rows_per_group(int) { return 112; }
-int launch_cube_alpha(const CubeArgs&, void*) { return 0; }
-int launch_cube_gamma(const CubeArgs&, void*) { return 0; }
+int launch_cube_alpha(const CubeArgs& c, void*) { g_alpha.push_back(c); return 0; }
+int launch_cube_gamma(const CubeArgs& c, void*) { g_gamma.push_back(c); return 0; }
 int cube_set_lds_limits() { return 0; }
-int launch_wigner(const WignerArgs&, Tile, void*) { return 0; }
+int launch_wigner(const WignerArgs& a, Tile, void*) { g_wigner.push_back(a); return 0; }
 int launch_fwd(const FwdArgs&, Tile, void*) { return 0; }
 int launch_beam_symmetry(const double*, int, int, int*, void*) { return 0; }
 int launch_adj(const AdjArgs&, Tile t, void*) { g_adj_tiles.push_back(t); return 0; }
@@ -230,6 +233,74 @@ void pageable_capture()
     }
 }
 
+// ------------------------------------------------------------------ launches of 2^32 work items and more
+// One launch holds fewer than 2^32 work items (the runtime lets a larger product wrap, and reports nothing):
+// larger calls take several, which together cover every element once.
+void launch_limits()
+{
+    const long long limit = 1LL << 32;
+    double* const out = reinterpret_cast<double*>(0x1000000);   // never dereferenced here
+    {
+        const int nring = 4500000;   // l = 0: two workgroups of 512 lanes per ring
+        std::vector<double> x(nring, 0.25);
+        const size_t n = wigner_d_matrix_workspace_bytes(0, nring);
+        Buffer w(n);
+        check(wigner_d_matrix_x(0, nring, x.data(), out, w.p, n, nullptr) == TC_OK, "wigner_d_matrix on 4500000 rings");
+        long long next = 0;
+        bool fits = true, follow = true;
+        for (const tc::MatrixArgs& a : g_matrix) {
+            fits = fits && (long long)a.ntile * 2 * a.nring * 512 < limit;
+            follow = follow && a.d == out + next && a.trig == g_matrix[0].trig + 2 * next && a.ring.x == g_matrix[0].ring.x + next &&
+                     a.ring.lch == g_matrix[0].ring.lch + next && a.ring.lcl == g_matrix[0].ring.lcl + next &&
+                     a.ring.lsh == g_matrix[0].ring.lsh + next && a.ring.lsl == g_matrix[0].ring.lsl + next &&
+                     a.lnA == g_matrix[0].lnA;
+            next += a.nring;
+        }
+        check(fits, "every launch below 2^32 work items");
+        check(follow && next == nring, "the launches follow each other over the rings");
+        fake::streams().clear();
+    }
+    {
+        const int nring = 1000, npair = 4300000;   // 8 workgroups of 128 lanes per pair
+        std::vector<double> x(nring, 0.25);
+        std::vector<int> mb(npair, 0);
+        const size_t n = totalconv_workspace_bytes_rings_x(TC_OP_WIGNER, 0, npair, nring, x.data());
+        Buffer w(n);
+        check(wigner_d_rings_x(0, npair, mb.data(), mb.data(), nring, x.data(), out, w.p, n, nullptr) == TC_OK,
+              "wigner_d_rings of 4300000 pairs");
+        long long next = 0;
+        bool fits = true, follow = true;
+        for (const tc::WignerArgs& a : g_wigner) {
+            fits = fits && (long long)a.npair * a.ntile * 128 < limit;
+            follow = follow && a.d == out + next * nring && a.col.mb == g_wigner[0].col.mb + next &&
+                     a.col.ms == g_wigner[0].col.ms + next && a.col.lnA == g_wigner[0].col.lnA + 2 * next &&
+                     a.nring == nring;
+            next += a.npair;
+        }
+        check(fits, "every launch below 2^32 work items");
+        check(follow && next == npair, "the launches follow each other over the pairs");
+        fake::streams().clear();
+    }
+    {
+        const int nring = 70000000;   // a chunk as long as the call, one alpha
+        tc_set_tile(TC_OP_CUBE, nring);
+        const size_t n = totalconv_datacube_workspace_bytes(0, 0, nring, 1, 2);
+        Buffer w(4096);
+        check(n > 0 && totalconv_datacube(0, 0, nring, out, 1, 2, out, w.p, n, nullptr) == TC_OK, "data cube of 70000000 rings");
+        tc_set_tile(TC_OP_CUBE, 0);
+        long long next = 0;
+        bool fits = true, follow = g_alpha.size() == g_gamma.size();
+        for (const tc::CubeArgs& c : g_gamma) {
+            fits = fits && (long long)c.nring_chunk * c.nalpha * 256 < limit;
+            follow = follow && c.ring0 == next;
+            next += c.nring_chunk;
+        }
+        check(fits && follow && next == nring, "its launches below 2^32 work items, one after the other over the rings");
+    }
+    check(per_launch(1, 256) == 16777215 && per_launch(3, 256) == 5592405 && per_launch(1LL << 40, 64) == 1,
+          "units per launch");
+}
+
 }  // namespace
 
 int main(int argc, char** argv)
@@ -239,6 +310,7 @@ int main(int argc, char** argv)
     else if (which == "image_streams") image_streams();
     else if (which == "image_capture") image_capture();
     else if (which == "pageable_capture") pageable_capture();
+    else if (which == "launch_limits") launch_limits();
     else check(false, "unknown check");
     if (g_failed) return 1;
     std::printf("ok\n");
