@@ -207,7 +207,8 @@ double walk_cost(int op, int R, int NT, int nslot)
 }
 
 // The tile of a call over nslot ring slots: R as set or, at 0, the cheapest built one, with the
-// cheapest number of lanes per workgroup for it.
+// cheapest number of lanes per workgroup for it.  The adjoint's smaller workgroups are built with TB 32: a TB 64
+// that was set keeps 256 lanes.
 tc::Tile fit_tile(int op, tc::Tile t, int nslot)
 {
     const int R0 = t.R;
@@ -215,11 +216,12 @@ tc::Tile fit_tile(int op, tc::Tile t, int nslot)
     for (int R : {8, 4, 2}) {
         if ((R0 > 0 && R != R0) || (op == TC_OP_FWD_POL && R > 4)) continue;
         for (int NT : {256, 128, 64}) {
+            if (op == TC_OP_ADJ && NT < 256 && g_tile_override[op].TB > 32) continue;
             const double c = walk_cost(op, R, NT, nslot);
             if (best == 0.0 || c < best) { best = c; t.R = R; t.NT = NT; }
         }
     }
-    if (op == TC_OP_ADJ && t.NT < 256) t.TB = 32;   // the blocks the smaller workgroups are built with
+    if (op == TC_OP_ADJ && t.NT < 256) t.TB = 32;
     return t;
 }
 

@@ -301,6 +301,52 @@ void launch_limits()
           "units per launch");
 }
 
+// ------------------------------------------------------------------ the adjoint's tile as it was set
+// A block size TB that was set is the one that runs, for calls and plans; where none is, small ring sets take
+// smaller workgroups (built with TB 32).
+void adjoint_tile()
+{
+    const int lmax = 12, mbmax = 2, nring = 9;
+    const std::vector<double> beta = grid(nring);
+    Buffer alm(16 * 91), blm(16 * 5 * 13), C(16 * 5 * 13 * nring), ab(16 * 91), bb(16 * 5 * 13);
+    const size_t n = totalconv_workspace_bytes(TC_OP_ADJ, lmax, mbmax, nring);
+    Buffer w(n);
+    auto call = [&] {
+        g_adj_tiles.clear();
+        check(totalconv_adj(lmax, mbmax, nring, beta.data(), alm.d(), blm.d(), C.d(), ab.d(), bb.d(), w.p, n, nullptr) ==
+                  TC_OK && g_adj_tiles.size() == 1, "call");
+        return g_adj_tiles.empty() ? tc::Tile{} : g_adj_tiles[0];
+    };
+    auto plan = [&] {
+        tc_detector d{};
+        d.lmax = lmax; d.mbmax = mbmax; d.nring = nring; d.beta = beta.data(); d.blm = blm.d(); d.Cbar = C.d();
+        d.blm_bar = bb.d();
+        void* p = nullptr;
+        g_adj_tiles.clear();
+        check(tc_plan_create(&p, TC_OP_ADJ, 1, &d, lmax, alm.d(), ab.d(), nullptr) == TC_OK && g_adj_tiles.size() == 1,
+              "plan");
+        tc_plan_destroy(p);
+        return g_adj_tiles.empty() ? tc::Tile{} : g_adj_tiles[0];
+    };
+    tc::Tile t = call();
+    check(t.NT < 256 && t.TB == 32, "nothing set: a small workgroup");
+    check(tc_set_tile_ex(TC_OP_ADJ, 0, 64, 0) == TC_OK, "TB 64");
+    t = call();
+    check(t.TB == 64 && t.NT == 256, "TB 64 runs");
+    t = plan();
+    check(t.TB == 64 && t.NT == 256, "and in a plan");
+    check(tc_set_tile_ex(TC_OP_ADJ, 4, 64, 4) == TC_OK, "R 4, TB 64");
+    t = call();
+    check(t.R == 4 && t.TB == 64 && t.NT == 256, "R 4 and TB 64 run");
+    check(tc_set_tile_ex(TC_OP_ADJ, 4, 32, 4) == TC_OK, "R 4, TB 32");
+    t = call();
+    check(t.R == 4 && t.TB == 32 && t.NT < 256, "TB 32 with a small workgroup");
+    check(tc_set_tile_ex(TC_OP_ADJ, 0, 0, 0) == TC_OK, "nothing set");
+    t = plan();
+    check(t.NT < 256 && t.TB == 32, "a small workgroup again");
+    hipDeviceSynchronize();
+}
+
 }  // namespace
 
 int main(int argc, char** argv)
@@ -311,6 +357,7 @@ int main(int argc, char** argv)
     else if (which == "image_capture") image_capture();
     else if (which == "pageable_capture") pageable_capture();
     else if (which == "launch_limits") launch_limits();
+    else if (which == "adjoint_tile") adjoint_tile();
     else check(false, "unknown check");
     if (g_failed) return 1;
     std::printf("ok\n");

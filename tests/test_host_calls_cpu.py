@@ -12,7 +12,7 @@ ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
 SAN = ["-O1", "-g", "-fno-omit-frame-pointer", "-fsanitize=address,undefined", "-fno-sanitize-recover=all"]
 ENV = dict(os.environ, ASAN_OPTIONS="detect_leaks=0:halt_on_error=1",
            UBSAN_OPTIONS="print_stacktrace=1:halt_on_error=1")
-CHECKS = ["gradient_order", "image_streams", "image_capture", "pageable_capture", "launch_limits"]
+CHECKS = ["gradient_order", "image_streams", "image_capture", "pageable_capture", "launch_limits", "adjoint_tile"]
 
 pytestmark = pytest.mark.skipif(shutil.which("g++") is None or not os.path.exists(os.path.join(ROCM, "include", "hip")),
                                 reason="no g++ or HIP headers")
