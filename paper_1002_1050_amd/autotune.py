@@ -7,19 +7,20 @@ kernel depends on it).
 Each candidate runs the real launch (after one untimed warm-up) and is timed with
 HIP events on the stream it runs on; the fastest wins.  Results are cached in a
 JSON file (``$TC_TUNE_CACHE``, else ``~/.cache/paper_1002_1050_amd/tiles.json``)
-keyed by the operation, sizes and GPU name, so a later process reuses them.
+keyed by the operation, sizes, GPU name and library build, so a later process reuses them.
 """
 from __future__ import annotations
 
+import hashlib
 import json
 import os
 
 from . import _binding as B
 
 CANDIDATES = {
-    B.TC_OP_FWD: [(r, tb, 4) for tb in (32, 64) for r in (2, 4, 8)],
+    B.TC_OP_FWD: [(r, 64, 4) for r in (2, 4, 8)],   # one build per R: TB shapes no forward kernel
     B.TC_OP_ADJ: [(r, tb, 4) for tb in (32, 64) for r in (2, 4, 8)],
-    B.TC_OP_FWD_POL: [(r, tb, 4) for tb in (32, 64) for r in (2, 4)],
+    B.TC_OP_FWD_POL: [(r, 64, 4) for r in (2, 4)],
 }
 
 
@@ -85,16 +86,24 @@ def _gpu_name():
     return torch.cuda.get_device_name(0).replace(" ", "_")
 
 
+def _build_id():
+    """Digest of the built library: a tile timed on other kernels is timed again."""
+    try:
+        with open(B.LIB_PATH, "rb") as f:
+            return hashlib.sha256(f.read()).hexdigest()[:16]
+    except OSError:
+        return "unbuilt"
+
+
 def tune_plain(op, lmax, mbmax, cosbeta, alm, blm, Cbar=None, reps=2, use_cache=True):
     """Best (R, TB, TR) for a plain totalconv_fwd / totalconv_adj / totalconv_fwd_pol call of this
     shape (for the polarised forward, alm and blm are the lists of pairs)."""
     npair = len(alm) if op == B.TC_OP_FWD_POL else 1
-    key = f"plain:{op}:{lmax}:{mbmax}:{len(cosbeta)}:{npair}:{_gpu_name()}"
+    key = f"plain:{op}:{lmax}:{mbmax}:{len(cosbeta)}:{npair}:{_gpu_name()}:{_build_id()}"
     cache = _load() if use_cache else {}
     if key in cache:
         return tuple(cache[key]["tile"])
     times = {}
-    default = B.get_tile_ex(op, lmax)
     try:
         for t in CANDIDATES[op]:
             B.set_tile_ex(op, *t)
@@ -116,14 +125,14 @@ def tune_plain(op, lmax, mbmax, cosbeta, alm, blm, Cbar=None, reps=2, use_cache=
         raise MemoryError(f"no tile of op {op} fits in device memory at lmax {lmax}, mbmax {mbmax}")
     best = min(times, key=times.get)
     cache = _load()
-    cache[key] = {"tile": list(best), "ms": {_key(k): v for k, v in times.items()}, "default": list(default)}
+    cache[key] = {"tile": list(best), "ms": {_key(k): v for k, v in times.items()}}
     _store(cache)
     return best
 
 
 def tune_plan(op, make_plan, reps=2, use_cache=True, key_extra=""):
     """Best (R, TB, TR) for a batched plan; make_plan() builds the plan for the current tile."""
-    key = f"plan:{op}:{key_extra}:{_gpu_name()}"
+    key = f"plan:{op}:{key_extra}:{_gpu_name()}:{_build_id()}"
     cache = _load() if use_cache else {}
     if key in cache:
         return tuple(cache[key]["tile"]), cache[key]["ms"]
