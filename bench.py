@@ -88,6 +88,13 @@ def hbm_traffic(kernel, workload, tile):
     return MEASURED_TRAFFIC.get(workload, {}).get(kernel, {}).get(",".join(str(int(v)) for v in tile))
 
 
+def given_tile(spec):
+    """(R, TB, TR) of a --tile-fwd / --tile-adj option; without one (0, 0, 0), the library's choice for
+    each call (what get_tile_ex answers is the start of the plans, not what a plain call takes)."""
+    v = [int(u) for u in spec.split(",")] if spec else [0, 0, 0]
+    return (v[0], v[1], v[2] if len(v) > 2 else 4)
+
+
 def parse():
     p = argparse.ArgumentParser(description=__doc__)
     p.add_argument("--gpus", type=int, default=1)
@@ -542,7 +549,7 @@ def polarised_compare(w, beta, alm, blm, reps, tune):
     dev = alm.device
     alms = [alm] + [torch.from_numpy(S.sky_alm(w.lmax, w.sky_seed + 1 + p)).to(dev) for p in range(2)]
     blms = [blm] + [torch.from_numpy(S.random_beam(w.lmax, w.mbmax, 77 + p)).to(dev) for p in range(2)]
-    tile = B.get_tile_ex(B.TC_OP_FWD_POL, w.lmax)
+    tile = given_tile("")
     if tune:
         from paper_1002_1050_amd import autotune
         tile = autotune.tune_plain(B.TC_OP_FWD_POL, w.lmax, w.mbmax, B.rings_from_beta(beta), alms, blms, reps=1)
@@ -634,22 +641,15 @@ def main():
     torch.cuda.synchronize()
     log("set-up done")
 
-    def given(spec):
-        v = [int(u) for u in spec.split(",")]
-        return (v[0], v[1], v[2] if len(v) > 2 else 4)
-
-    tf = given(args.tile_fwd) if args.tile_fwd else None
-    ta = given(args.tile_adj) if args.tile_adj else None
-    if not args.no_tune and (tf is None or ta is None):
+    tf, ta = given_tile(args.tile_fwd), given_tile(args.tile_adj)
+    if not args.no_tune and not (args.tile_fwd and args.tile_adj):
         from paper_1002_1050_amd import autotune
-        if tf is None:
+        if not args.tile_fwd:
             tf = autotune.tune_plain(B.TC_OP_FWD, w.lmax, w.mbmax, x, alm, blm, reps=1)
-        if ta is None:
+        if not args.tile_adj:
             ta = autotune.tune_plain(B.TC_OP_ADJ, w.lmax, w.mbmax, x, alm, blm, G, reps=1)
         log(f"autotuned tiles (R, TB, TR): forward {tf}, adjoint {ta}")
         torch.cuda.empty_cache()
-    tf = tf or B.get_tile_ex(B.TC_OP_FWD, w.lmax)
-    ta = ta or B.get_tile_ex(B.TC_OP_ADJ, w.lmax)
     B.set_tile_ex(B.TC_OP_FWD, *tf)
     B.set_tile_ex(B.TC_OP_ADJ, *ta)
     tiles = {"forward": list(tf), "adjoint": list(ta)}

@@ -292,31 +292,40 @@ int totalconv_datacube(int lmax, int mbmax, int nring, const double* C, int nalp
 
 /*
  * Tile selection for later calls in this process (not in the paper; a tuning
- * knob of this implementation).  Each lane walks R chains; a workgroup covers
- * 256*R ring slots of one column.  op = TC_OP_FWD or TC_OP_ADJ (R in {2, 4, 8}),
- * TC_OP_FWD_POL (R in {2, 4}), TC_OP_WIGNER (R in {1, 4}) or TC_OP_MATRIX (R in {1, 2}), the last
- * two accepted without effect (one shape is built); for TC_OP_CUBE, R > 0 sets the rings the data cube processes per chunk
- * (and so its workspace).  R = 0 restores the built-in choice.  Affects
- * the workspace sizes reported afterwards.  Returns TC_EINVAL for other values.
+ * knob of this implementation).  Each lane walks R chains; a workgroup of 64, 128
+ * or 256 lanes (the library's choice by the ring slots of the call) covers
+ * lanes * R ring slots of one column.  op = TC_OP_FWD or TC_OP_ADJ (R in {2, 4, 8}),
+ * TC_OP_FWD_POL (R in {2, 4}), TC_OP_WIGNER (R in {1, 4}) or TC_OP_MATRIX (R in
+ * {1, 2}), the last two accepted without effect (one shape is built); for TC_OP_CUBE,
+ * R > 0 sets the rings the data cube processes per chunk (and so its workspace).
+ * R = 0 restores the built-in choice, which for the convolutions goes by the ring
+ * slots of each call.  Affects the workspace sizes of the data cube reported
+ * afterwards.  Returns TC_EINVAL for other values.
  * Not synchronised: set it from the thread that issues the calls.
  */
 int tc_set_tile(int op, int R);
 
 /*
- * Full tile selection: R chains per lane, TB values of l per LDS coefficient
- * block (32 or 64) and TR (4, the only built value; kept so that tiles stay
- * (R, TB, TR) triples).  0 keeps the built-in value of a parameter.  Same
- * scope and rules as tc_set_tile; TC_EINVAL for combinations that are not built.
+ * Full tile selection: R chains per lane, TB values of l per block of the
+ * adjoint's sums (32 or 64; shapes no other kernel; 64 takes 256 lanes) and TR (4,
+ * the only value; shapes no kernel, kept so that tiles stay (R, TB, TR) triples).
+ * 0 keeps the built-in value of a parameter.  Same scope and rules as tc_set_tile;
+ * TC_EINVAL for combinations that are not built.
  */
 int tc_set_tile_ex(int op, int R, int TB, int TR);
 
-/* The R that the next call of `op` at this lmax would use. */
+/*
+ * The R of op as set; where none is set, the R that a batched plan of op starts
+ * from (for lmax >= 256; below, a fixed 2).  A plain convolution call without a set
+ * R picks its own by its ring slots, which this query is not given: to return to
+ * that choice set R = 0, not the value read here.
+ */
 int tc_get_tile(int op, int lmax);
 
 /*
- * The full tile (R, TB, TR) of op at this lmax: as set, else the built-in one for rings that fill
- * its workgroups.  Where R is not set, a convolution call picks R (2, 4 or 8) and the lanes per
- * workgroup (64, 128 or 256; TB is 32 below 256 in the adjoint) by its number of ring slots.
+ * The full tile (R, TB, TR), R as tc_get_tile answers it.  TB: as set, else 32 below
+ * lmax 256 and 64 from there on (in the adjoint 32 wherever a call takes fewer than
+ * 256 lanes).
  */
 int tc_get_tile_ex(int op, int lmax, int* R, int* TB, int* TR);
 

@@ -461,11 +461,12 @@ def set_tile(op: int, R: int):
 
 
 def get_tile(op: int, lmax: int) -> int:
+    """R as set, else the start of a plan's choice (a plain call picks its R by its ring slots)."""
     return int(lib().tc_get_tile(op, lmax))
 
 
 def set_tile_ex(op: int, R: int = 0, TB: int = 0, TR: int = 0):
-    """Chains per lane R, l-block TB and adjoint reduction block TR for later calls; 0 = built-in."""
+    """Chains per lane R, the adjoint's l block TB, and TR (no effect) for later calls; 0 = built-in."""
     _check("tc_set_tile_ex", lib().tc_set_tile_ex(op, R, TB, TR))
 
 
