@@ -881,7 +881,7 @@ __global__ void __launch_bounds__(NT, (fwd_min_waves<R, NC, NP>())) k_fwd(const 
     __shared__ FwdShared<NT, coef_slots<NC, false>()> sh;
     const int ci = blockIdx.x / a.ntile;
     if constexpr (NC == 1 && NP == 1) {
-        if (a.beam_sym[0] && row_sign(a, 0, ldg(a.col.mb + ci)) != 0) return;
+        if (row_sign(a, 0, ldg(a.col.mb + ci)) != 0) return;
     }
     int s[NC] = {};
     if constexpr (NC > 1) {   // k_fwd_pol_rows's columns
@@ -1645,7 +1645,7 @@ bool tile_supported(int op, Tile t)
     const bool nt_ok = t.NT == 64 || t.NT == 128 || t.NT == 256;
     const bool tb_ok = t.TB == 32 || t.TB == 64;
     const bool r_ok = t.R == 2 || t.R == 4 || t.R == 8;
-    if (op == 0) return (t.R == 1 || t.R == 4) && t.TB == 32 && t.NT == 256;
+    if (op == 0) return (t.R == 1 || t.R == 4) && t.TB == 32;
     if (op == 1) return r_ok && tb_ok && nt_ok;
     if (op == 2) return r_ok && tb_ok && t.TR == 4 && (t.NT == 256 || (nt_ok && t.TB == 32));
     if (op == 3) return (t.R == 2 || t.R == 4) && tb_ok && nt_ok;
@@ -1686,20 +1686,40 @@ int launch_prep(const PrepArgs& a, void* stream)
     return (int)hipGetLastError();
 }
 
+// The scalar forward of one column set: for NT < 256 one launch of both forms, else one of each.
+template <int R, int NT>
+static int launch_fwd_scalar(const FwdArgs& a, void* stream)
+{
+    const int blocks = a.ncol * a.ntile;
+    if constexpr (NT < 256) {
+        return launch_grid(k_fwd_either<R, NT>, a, blocks, NT, stream);
+    } else {
+        const int rc = launch_grid(k_fwd_rows<R, NT>, a, blocks, NT, stream);
+        return rc ? rc : launch_grid(k_fwd<R, NT, 1, 1>, a, blocks, NT, stream);
+    }
+}
+
+// The adjoint's columns; with row signs (the sky gradient alone) the same split.
+template <int R, int NT, int TB>
+static int launch_adj_columns(const AdjArgs& a, void* stream)
+{
+    if (a.beam_sym) {
+        if constexpr (NT < 256) {
+            return launch_grid(k_adj_either<R, NT, TB>, a, a.ncol, NT, stream);
+        } else {
+            const int rc = launch_grid(k_adj_one_sum<R, NT, TB>, a, a.ncol, NT, stream);
+            if (rc) return rc;
+        }
+    }
+    return launch_grid(k_adj<R, NT, TB>, a, a.ncol, NT, stream);   // every ring tile of a column in one workgroup
+}
+
 int launch_fwd(const FwdArgs& a, Tile t, void* stream)
 {
     const int blocks = a.ncol * a.ntile;
     if (a.npair == 1) {
-#define X(r, nt)                                                                              \
-    if (t.R == r && t.NT == nt) {                                                             \
-        if constexpr (nt < 256)                                                               \
-            if (a.beam_sym[0]) return launch_grid(k_fwd_either<r, nt>, a, blocks, nt, stream); \
-        if (a.beam_sym[0]) {                                                                  \
-            const int rc = launch_grid(k_fwd_rows<r, nt>, a, blocks, nt, stream);             \
-            if (rc) return rc;                                                                \
-        }                                                                                     \
-        return launch_grid(k_fwd<r, nt, 1, 1>, a, blocks, nt, stream);                        \
-    }
+        if (!a.beam_sym[0]) return (int)hipErrorInvalidValue;   // a call of one pair always has its row signs
+#define X(r, nt) if (t.R == r && t.NT == nt) return launch_fwd_scalar<r, nt>(a, stream);
         TC_FWD_VARIANTS(X)
 #undef X
         return (int)hipErrorInvalidValue;
@@ -1722,17 +1742,7 @@ int launch_fwd(const FwdArgs& a, Tile t, void* stream)
 
 int launch_adj(const AdjArgs& a, Tile t, void* stream)
 {
-    const int blocks = a.ncol;   // every ring tile of a column in one workgroup
-#define X(r, nt, tb)                                                                          \
-    if (t.R == r && t.NT == nt && t.TB == tb) {                                               \
-        if constexpr (nt < 256)                                                               \
-            if (a.beam_sym) return launch_grid(k_adj_either<r, nt, tb>, a, blocks, nt, stream); \
-        if (a.beam_sym) {                                                                     \
-            const int rc = launch_grid(k_adj_one_sum<r, nt, tb>, a, blocks, nt, stream);      \
-            if (rc) return rc;                                                                \
-        }                                                                                     \
-        return launch_grid(k_adj<r, nt, tb>, a, blocks, nt, stream);                          \
-    }
+#define X(r, nt, tb) if (t.R == r && t.NT == nt && t.TB == tb) return launch_adj_columns<r, nt, tb>(a, stream);
     TC_ADJ_VARIANTS(X)
 #undef X
     return (int)hipErrorInvalidValue;
