@@ -143,10 +143,12 @@ def _require_device(t, name, dtype):
 
 
 class _Workspace:
-    """Grow-only device workspace per (device, stream)."""
+    """Grow-only device workspace per (device, stream).  One that a captured call uses is written again by every
+    replay of its graph: it is kept, also when a larger one takes its place, until clear()."""
 
     def __init__(self):
         self._bufs = {}
+        self._captured = {}
 
     def get(self, torch, device, stream, nbytes):
         key = (device.index, stream.value)
@@ -155,10 +157,13 @@ class _Workspace:
             self._bufs.pop(key, None)
             buf = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
             self._bufs[key] = buf
+        if torch.cuda.is_current_stream_capturing():
+            self._captured[id(buf)] = buf
         return buf
 
     def clear(self):
         self._bufs.clear()
+        self._captured.clear()
 
 
 workspace_cache = _Workspace()

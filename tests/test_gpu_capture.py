@@ -67,3 +67,29 @@ def test_captured_calls_with_pageable_tables(B):
     replays(B, "totalconv_fwd_noalloc", noalloc, 3)
     replays(B, "wigner_d_matrix", lambda: [B.wigner_d_matrix(L, beta)], 3)
     replays(B, "totalconv_datacube", lambda: [B.totalconv_datacube(L, M, C, 5, 128)], 3)
+
+
+def test_replay_keeps_off_other_memory(B):
+    """A larger call on the stream replaces the workspace; the captured call's stays its own."""
+    L, M, nring = 30, 2, 41
+    beta = S.ring_colatitudes(nring)
+    alm, blm = dev(S.sky_alm(L, 1)), dev(S.random_beam(L, M, 2))
+    s, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    B.workspace_cache.clear()
+    with torch.cuda.stream(s):
+        want = B.totalconv_fwd(L, M, beta, alm, blm)
+        used = B.workspace_cache.get(torch, alm.device, B._stream_handle(torch, alm.device), 1)
+    torch.cuda.synchronize()
+    print("[gpu] capture, larger call, replay", flush=True)
+    with torch.cuda.graph(graph, stream=s):
+        out = B.totalconv_fwd(L, M, beta, alm, blm)
+    where, size = used.data_ptr(), used.numel()
+    del used
+    with torch.cuda.stream(s):
+        B.totalconv_fwd(400, 4, S.ring_colatitudes(500), dev(S.sky_alm(400, 3)), dev(S.random_beam(400, 4, 4)))
+        fresh = [torch.full((size,), 7, dtype=torch.uint8, device="cuda") for _ in range(8)]
+    torch.cuda.synchronize()
+    assert all(t.data_ptr() != where for t in fresh)
+    graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(out, want) and all(bool((t == 7).all()) for t in fresh)
