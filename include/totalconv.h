@@ -202,7 +202,9 @@ int totalconv_fwd_noalloc(int lmax, int mbmax, int nring, const double* beta,
  *   alm_bar_{l,msky} = sum_{mb,j} b_{l,mb} d^l_{mb,msky}(beta_j) Cbar_{mb,msky,j}
  *   blm_bar_{l,mb}   = sum_{msky,j} s_{l,msky} d^l_{mb,msky}(beta_j) conj(Cbar_{mb,msky,j})
  * d is recomputed on the fly.  alm_bar (layout of alm) and blm_bar (layout of blm)
- * may each be NULL; blm_bar entries with l < |mb| are written as 0.
+ * may each be NULL; blm_bar entries with l < |mb| are written as 0.  blm_bar may be
+ * blm itself.  With blm_bar NULL, columns whose beam rows mb and -mb are equal up to a
+ * sign form one sum over the rings instead of two, which changes only the rounding.
  *   workspace    at least totalconv_workspace_bytes(TC_OP_ADJ, lmax, mbmax, nring) bytes
  */
 int totalconv_adj(int lmax, int mbmax, int nring, const double* beta,
@@ -246,8 +248,8 @@ int totalconv_fwd_pol_x(int lmax, int mbmax, int nring, const double* cosbeta, i
  * totalconv_adj gives them for that pair's sky, beam and cotangent.  In
  * TC_POL_SUM mode the pairs share one reduction over the rings and one launch
  * forms every pair's sky gradient from it (each equal, bit for bit, to what
- * totalconv_adj returns for that pair and the one cotangent); in
- * TC_POL_SEPARATE mode the cotangents are reduced one after the other.
+ * totalconv_adj returns for that pair and the one cotangent when it forms both
+ * gradients); in TC_POL_SEPARATE mode the cotangents are reduced one after the other.
  *   workspace    at least totalconv_workspace_bytes(TC_OP_ADJ, lmax, mbmax, nring) bytes
  */
 int totalconv_adj_pol(int lmax, int mbmax, int nring, const double* beta, int npair,

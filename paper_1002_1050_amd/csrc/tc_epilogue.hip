@@ -2,8 +2,9 @@
 // per-column sums U, V: the polarised adjoint with summed outputs (the pairs' outputs add into
 // one C, footnote of Sec. 4.1).  One launch reads U and V once for all pairs, where one launch
 // per pair would read them once per pair.  Every pair's sums take the operations of the one-pair
-// sky epilogue (k_adj_sky) in the same order, so each sky gradient equals, bit for bit, the one a
-// scalar adjoint of the same cotangent returns for that pair.  (The beam gradients keep one
+// sky epilogue (k_adj_grads' sky part) in the same order, so each sky gradient equals, bit for bit, the one
+// a scalar adjoint of the same cotangent returns for that pair with both gradients (with the sky
+// gradient alone it may form one sum per column instead of U and V).  (The beam gradients keep one
 // launch per pair: a kernel that summed all three pairs' beam gradients in one pass over U, V
 // ran 6.8 ms at lmax 4096, against 3 x 2.1 ms for one launch per pair.)
 //
