@@ -341,8 +341,8 @@ int tc_get_tile_ex(int op, int lmax, int* R, int* TB, int* TR);
  * adjoint two per walk at TB 32 and R <= 4 (at R 8 the second detector's
  * cotangents do not fit the registers), one walk adding into both detectors'
  * sums.  One workgroup per work item (walk, column, ring tile), the items
- * longest first.  Forward: one launch per chains-per-lane R, the launches of
- * different R on parallel graph branches.  Adjoint: one launch per (R, lmax)
+ * longest first.  Forward: one launch per workgroup shape (R, lanes), the launches
+ * on parallel graph branches.  Adjoint: one launch per (R, lanes, lmax)
  * group, the groups one after the other; after each, a second stream runs its
  * detectors' beam gradients and adds their sky gradients to alm_bar (always in
  * the same order) beside the next group's walks.  Every beam gradient and forward
@@ -373,7 +373,8 @@ typedef struct tc_detector {
  * beams, sky and cotangents afresh (including, for the forward, which beam rows
  * are equal up to a sign, as totalconv_fwd does).  A detector is walked with the
  * largest R not above the plan's (tc_plan_tile) whose 256 R ring slots its rings
- * still fill more than half of (R halved while 128 R >= its slots).
+ * still fill more than half of (R halved while 128 R >= its slots), in workgroups of
+ * 64, 128 or 256 lanes as a plain call of that R.
  */
 int tc_plan_create(void** plan, int op, int ndet, const tc_detector* dets, int lmax_sky,
                    const double* alm, double* alm_bar, void* stream);
@@ -395,8 +396,8 @@ int tc_plan_destroy(void* plan);
  * totalconv_fwd_pol call records one pair (under op TC_OP_WIGNER, TC_OP_FWD,
  * TC_OP_ADJ, TC_OP_FWD_POL) on its own stream, directly before and after its
  * recursion kernel; totalconv_datacube records one TC_OP_CUBE pair around all
- * of its kernels (both streams), wigner_d_matrix one TC_OP_MATRIX pair (for the adjoint: without the two short epilogue kernels
- * that finish the gradients; totalconv_adj_pol records one TC_OP_ADJ pair per
+ * of its kernels, wigner_d_matrix one TC_OP_MATRIX pair (for the adjoint: without the short epilogue
+ * that finishes the gradients; totalconv_adj_pol records one TC_OP_ADJ pair per
  * cotangent), reusing the pairs cyclically.  n = 0 releases the events and
  * stops the recording.  Calls must then run on streams of that device.
  * Returns TC_OK, TC_EINVAL for n < 0 or n > 65536, TC_EHIP if event creation

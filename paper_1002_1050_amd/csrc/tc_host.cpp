@@ -1383,10 +1383,11 @@ int fwd_noalloc(int lmax, int mbmax, int nring, const double* beta, const double
 //
 // A plan holds, in one device allocation, the tables of every walk, the kernel-argument
 // records, the work items sorted by cost (longest first) and, for the adjoint, the partial
-// sums.  Forward walks are groups of up to kMaxPairs detectors that share lmax and rings (one
-// recursion feeds each member's output); every adjoint detector walks alone.  The plan's graph
-// is: [beam row signs ->] one launch over the items [-> sky-gradient epilogue over all
-// detectors -> per-detector beam-gradient epilogues].
+// sums.  A walk serves several detectors that share lmax and rings: in the forward up to
+// fwd_walk_pairs of its tile (one recursion feeds each member's output), in the adjoint
+// adj_walk_pairs_of.  Forward graph: beam row signs, then one launch per (R, NT) of the walks, side by
+// side.  Adjoint graph: one launch per (R, NT, lmax), one after the other, each followed on a second
+// stream by its detectors' sky gradients (one launch) and beam gradients (one each).
 
 struct tc_plan_s {
     int op = 0;
@@ -1447,7 +1448,7 @@ int check_detector(int i, const tc_detector& d, int op, int lmax_sky)
 }
 
 // R of a walk over nslot ring slots: the plan's R, halved while half of it still covers every
-// slot in one ring tile (the lanes of a workgroup that hold no ring would walk for nothing).
+// slot in one ring tile of 256 lanes (fit_tile then takes the lanes).
 int walk_R(const tc::Tile& t, int nslot)
 {
     int R = t.R;
@@ -1571,7 +1572,7 @@ int tc_plan_create(void** plan, int op, int ndet, const tc_detector* dets, int l
     std::vector<tc::FwdArgs> fa(op == TC_OP_FWD ? nwalk : 0);
     std::vector<tc::AdjArgs> aa(op == TC_OP_ADJ ? nwalk : 0);
     std::vector<tc::EpiArgs> ea(ndet);
-    // Launch groups: the walks of one R (forward), of one R and one lmax (adjoint: each group's
+    // Launch groups: the walks of one R and NT (forward), and of one lmax too (adjoint: each group's
     // epilogues run beside the next group's walks).
     struct Group { int R, NT, lmax; tc::Tile tile; long long cost; std::vector<int> walks; };
     std::vector<Group> groups;

@@ -12,9 +12,9 @@ namespace tc {
 // NT*R ring slots of one column.
 struct Tile {
     int R;    // chains per lane
-    int NT;   // lanes per workgroup
-    int TB;   // l values per LDS coefficient block
-    int TR;   // adjoint: steps per wave reduction of the lane sums
+    int NT;   // lanes per workgroup, and values of l staged at a time
+    int TB;   // adjoint: row times per block of emitted sums; shapes no other kernel
+    int TR;   // 4; shapes no kernel (tiles are (R, TB, TR) triples in the ABI)
 };
 
 // Device-resident per-call tables, all inside the caller's workspace.
@@ -59,8 +59,8 @@ struct FwdArgs {
     const double* blm[kMaxPairs];  // [2 pmbmax+1][L+1] complex, per pair
     double* C[kMaxPairs];          // [2 pmbmax+1][L+1][nring] complex, per output
     const int* beam_sym[kMaxPairs];  // scalar convolution: per beam row mb + pmbmax, s = +-1 if
-                           // b_{l,-mb} = s b_{l,mb} for every l >= |mb|, else 0 (from k_beam_symmetry);
-                           // null: not used.  Polarised with separate outputs: [0] holds per row a word
+                           // b_{l,-mb} = s b_{l,mb} for every l >= |mb|, else 0 (from launch_prep, in plans from
+                           // launch_beam_symmetry).  Polarised with separate outputs: [0] holds per row a word
                            // with pair p's sign + 1 in byte p (from launch_prep); summed: null
 };
 

@@ -381,7 +381,7 @@ __device__ __forceinline__ size_t packed_index(int lmax, int l, int m)
 
 // ================================================================ wigner_d_rings
 // One lane walks one ring of one (mb, msky) pair and stores d^l for every l: NT consecutive rings
-// of a row leave as 512-byte pieces per wave.  A call has few chains (9 pairs on 2001 rings: 284
+// of a row leave as 512-byte pieces per wave.  A call has few chains (9 pairs on 2001 rings: 288
 // waves on 1024 SIMDs) and up to lmax + 1 steps each, so it is bound by the latency of a step and,
 // with many pairs, by the stores; one chain per lane spreads the walks over the most SIMDs, and NT
 // lanes stage NT values of l at a time.  9 pairs on 2001 rings at lmax 1500: 63 us, 3.4 TB/s of stores
@@ -872,9 +872,10 @@ __device__ __forceinline__ bool pol_row_signs(const FwdArgs& a, int mb, int (&s)
     return all(mb);
 }
 
-// The scalar forward runs as two launches over every (column, tile): k_fwd_rows takes the
-// columns whose beam rows are equal up to a sign, k_fwd the others (and every polarised
-// column); a workgroup whose column belongs to the other launch returns at once.
+// The scalar forward with 256 lanes runs as two launches over every (column, tile): k_fwd_rows takes
+// the columns whose beam rows are equal up to a sign, k_fwd the others; a workgroup whose column belongs
+// to the other launch returns at once.  Polarised pairs with separate outputs are split the same way
+// between k_fwd_pol_rows and k_fwd; summed pairs take k_fwd alone.
 template <int R, int NT, int NC, int NP>
 __global__ void __launch_bounds__(NT, (fwd_min_waves<R, NC, NP>())) k_fwd(const FwdArgs a)
 {
