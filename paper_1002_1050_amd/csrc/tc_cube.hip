@@ -9,8 +9,8 @@
 //
 // Two passes over each chunk of rings, both bound by HBM bandwidth.  At lmax 2048, mbmax 14, 2000 rings,
 // 29 x 4096 angles (1.9 GB of C in, 1.9 GB of P out and in, 1.9 GB of cube out) they take 0.93 and 0.85 ms,
-// 4.1 and 4.5 TB/s of reads and writes together (2.53 ms before the rows of P were padded to whole lines, the
-// passes taken one after the other and the gamma pass given workgroups of the row's size, the sum over mb over single values; 1.84 ms the call now):
+// 4.1 and 4.5 TB/s of reads and writes together; the call 1.77 ms (2.42 ms with unpadded rows of P, the passes
+// side by side in smaller chunks, gamma workgroups of 256 lanes for every row and a sum over mb term by term):
 //  1. k_cube_alpha: P[j][a][k] = sum_mb e^{-i mb alpha_a} C[mb][k][j] for k = msky >= 0 -- the
 //     short sum over mb, done directly over pairs (mb, -mb) and (alpha, -alpha) with the host's
 //     table of phases, and the transpose from ring-fastest C to rows (ring, alpha) with msky

@@ -854,8 +854,8 @@ MatrixLayout make_matrix_layout(int l, int nring)
 // call's stream: side by side (the FFTs of a chunk on a second stream, next to the alpha pass of the next) both
 // passes, bound by memory alone, took no less together, and two buffers left chunks of half the size.  Larger
 // chunks spend less on the ramps and tails of their launches: 2000 rings at lmax 2048 (1.9 GB of sums) take
-// 2.28 ms by 500 rings, 1.95 ms at once; 4000 at lmax 4096 8.43 ms by 500 and 7.85 ms at once.  (Chunks that
-// stay in the 256 MB last-level cache, 64 or 128 rings, lose far more to the ramps than the cache saves.)
+// 1.99 ms by 500 rings, 1.89 ms at once; 4000 at lmax 4096 7.21 ms by 500 and 6.99 ms at once.  (Chunks that
+// stay in the 256 MB last-level cache lose more to the ramps than the cache saves: 2.55 ms by 64 rings.)
 constexpr size_t kCubeSumBytes = (size_t)2 << 30;
 constexpr size_t kCubeOldSumBytes = (size_t)768 << 20;
 

@@ -87,7 +87,7 @@ __device__ __forceinline__ void row_seed(double lnAh, double lnAl, int p, int q,
 // Two of the eight waves walk 128 steps into LDS, then all eight store the four images 16 bytes per
 // lane; the walk of the next 128 steps runs while those stores drain.  l = 4096 on 16 rings (8.6 GB):
 // 2.87 ms with two waves that walked, stored images 1 and 3 step by step and the others every 128 steps;
-// 2.78 ms with eight waves storing whole pieces wherever their lines lay; now 1.94 ms, 4.4 TB/s.
+// 2.78 ms with eight waves storing whole pieces wherever their lines lay; now 1.87 ms, 4.6 TB/s.
 constexpr int M_NT = kMatrixLanes, ROWS = 128, OWN = 112, FL = 128, RING = FL + 16;
 constexpr int LINE = 16;   // doubles per line
 
